@@ -26,6 +26,7 @@ struct LandscapeHost {
   uint8_t forest = 1;
   uint4 *rec = nullptr;
   double *cov = nullptr;  // [H*W][2] psi, slope/100, then [H*W][8] omega
+  uint4 *fcov = nullptr;  // [H*W] binary32 covariates of the coin filter
   uint32_t *blocked = nullptr;
   uint8_t *burn_steps = nullptr;  // device [256], NULL = one step for every type
   // observed share of simulations that left their LDS window (moving
@@ -210,6 +211,7 @@ fire_status sync_tables(fire_ctx *c) {
     d.rec = L.rec; d.ps = L.cov;
     d.omega = L.cov ? L.cov + 2 * (int64_t)L.W * L.H : nullptr;
     d.blocked = L.blocked;
+    d.fcov = L.fcov;
     d.burn_steps = L.burn_steps;
     d.forest_class = L.forest;
     hl[i] = d;
@@ -846,6 +848,7 @@ void fire_ctx_destroy(fire_ctx *c) {
   for (auto &L : c->ls) {
     if (L.rec) (void)hipFree(L.rec);
     if (L.cov) (void)hipFree(L.cov);
+    if (L.fcov) (void)hipFree(L.fcov);
     if (L.blocked) (void)hipFree(L.blocked);
     if (L.burn_steps) (void)hipFree(L.burn_steps);
   }
@@ -955,6 +958,7 @@ fire_status fire_landscape_load(fire_ctx *c, const fire_landscape_desc *d,
   float *d_f = nullptr;
   hipError_t e = hipMalloc(&L.rec, sizeof(uint4) * n);
   if (e == hipSuccess) e = hipMalloc(&L.cov, sizeof(double) * 10 * n);
+  if (e == hipSuccess) e = hipMalloc(&L.fcov, sizeof(uint4) * n);
   if (e == hipSuccess) e = hipMalloc(&L.blocked, sizeof(uint32_t) * H * stride);
   if (e == hipSuccess) e = hipMalloc(&d_veg, n);
   if (e == hipSuccess) e = hipMalloc(&d_f, sizeof(float) * 4 * n);
@@ -964,12 +968,15 @@ fire_status fire_landscape_load(fire_ctx *c, const fire_landscape_desc *d,
   if (e == hipSuccess)
     e = launch_preprocess(d_veg, d_f, d_f + n, d_f + 2 * n, d_f + 3 * n, W, H,
                           stride, L.rec, L.cov, L.cov + 2 * n, L.blocked, nullptr);
+  if (e == hipSuccess)
+    e = launch_fcov(L.rec, L.cov, L.cov + 2 * n, n, L.forest, L.fcov, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (d_veg) (void)hipFree(d_veg);
   if (d_f) (void)hipFree(d_f);
   if (e != hipSuccess) {
     if (L.rec) (void)hipFree(L.rec);
     if (L.cov) (void)hipFree(L.cov);
+    if (L.fcov) (void)hipFree(L.fcov);
     if (L.blocked) (void)hipFree(L.blocked);
     if (L.burn_steps) (void)hipFree(L.burn_steps);
     return fail(c, e == hipErrorOutOfMemory ? FIRE_E_OOM : FIRE_E_DEVICE,
@@ -994,7 +1001,7 @@ fire_status fire_landscape_free(fire_ctx *c, int32_t id) {
   HIP_OR_FAIL(c, hipSetDevice(c->device));
   HIP_OR_FAIL(c, hipDeviceSynchronize());
   LandscapeHost &L = c->ls[id];
-  (void)hipFree(L.rec); (void)hipFree(L.cov); (void)hipFree(L.blocked);
+  (void)hipFree(L.rec); (void)hipFree(L.cov); (void)hipFree(L.fcov); (void)hipFree(L.blocked);
   if (L.burn_steps) (void)hipFree(L.burn_steps);
   L = LandscapeHost();
   for (auto &T : c->tg)

@@ -24,6 +24,8 @@ struct LandscapeDev {
                                 // active steps of a burning cell by veg value
   uint32_t forest_class;
   uint32_t pad0;
+  const uint4 *fcov;            // [H*W] binary32 covariates of the coin filter
+                                // (fcov_kernel)
 };
 
 struct TargetDev {
@@ -76,6 +78,8 @@ hipError_t launch_preprocess(const uint8_t *veg, const float *elev,
                              const float *wind, int W, int H, int stride,
                              uint4 *rec, double *ps, double *omega, uint32_t *blocked,
                              hipStream_t s);
+hipError_t launch_fcov(const uint4 *rec, const double *ps, const double *omega, int64_t n,
+                       uint32_t forest, uint4 *out, hipStream_t s);
 hipError_t launch_thresholds(const LandscapeDev *ls_dev_entry, int W, int H,
                              const double *beta_dev, uint32_t forest,
                              uint32_t *out, hipStream_t s);

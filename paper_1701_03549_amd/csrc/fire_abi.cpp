@@ -25,8 +25,8 @@ struct LandscapeHost {
   int W = 0, H = 0, stride = 0;
   uint8_t forest = 1;
   uint4 *rec = nullptr;
-  double *cov = nullptr;  // [H*W][2] psi, slope/100, then [H*W][8] omega
-  uint4 *fcov = nullptr;  // [H*W] binary32 covariates of the coin filter
+  double *cov = nullptr;  // [H*W][2] psi, slope/100, [H*W][8] omega, then fcov
+  uint4 *fcov = nullptr;  // [H*W] binary32 covariates of the coin filter (in cov)
   uint32_t *blocked = nullptr;
   uint8_t *burn_steps = nullptr;  // device [256], NULL = one step for every type
   // observed share of simulations that left their LDS window (moving
@@ -848,7 +848,6 @@ void fire_ctx_destroy(fire_ctx *c) {
   for (auto &L : c->ls) {
     if (L.rec) (void)hipFree(L.rec);
     if (L.cov) (void)hipFree(L.cov);
-    if (L.fcov) (void)hipFree(L.fcov);
     if (L.blocked) (void)hipFree(L.blocked);
     if (L.burn_steps) (void)hipFree(L.burn_steps);
   }
@@ -957,8 +956,9 @@ fire_status fire_landscape_load(fire_ctx *c, const fire_landscape_desc *d,
   uint8_t *d_veg = nullptr;
   float *d_f = nullptr;
   hipError_t e = hipMalloc(&L.rec, sizeof(uint4) * n);
-  if (e == hipSuccess) e = hipMalloc(&L.cov, sizeof(double) * 10 * n);
-  if (e == hipSuccess) e = hipMalloc(&L.fcov, sizeof(uint4) * n);
+  // the binary64 covariates and the coin filter's, in one allocation
+  if (e == hipSuccess) e = hipMalloc(&L.cov, (sizeof(double) * 10 + sizeof(uint4)) * n);
+  if (e == hipSuccess) L.fcov = reinterpret_cast<uint4 *>(L.cov + 10 * n);
   if (e == hipSuccess) e = hipMalloc(&L.blocked, sizeof(uint32_t) * H * stride);
   if (e == hipSuccess) e = hipMalloc(&d_veg, n);
   if (e == hipSuccess) e = hipMalloc(&d_f, sizeof(float) * 4 * n);
@@ -976,7 +976,6 @@ fire_status fire_landscape_load(fire_ctx *c, const fire_landscape_desc *d,
   if (e != hipSuccess) {
     if (L.rec) (void)hipFree(L.rec);
     if (L.cov) (void)hipFree(L.cov);
-    if (L.fcov) (void)hipFree(L.fcov);
     if (L.blocked) (void)hipFree(L.blocked);
     if (L.burn_steps) (void)hipFree(L.burn_steps);
     return fail(c, e == hipErrorOutOfMemory ? FIRE_E_OOM : FIRE_E_DEVICE,
@@ -1001,7 +1000,7 @@ fire_status fire_landscape_free(fire_ctx *c, int32_t id) {
   HIP_OR_FAIL(c, hipSetDevice(c->device));
   HIP_OR_FAIL(c, hipDeviceSynchronize());
   LandscapeHost &L = c->ls[id];
-  (void)hipFree(L.rec); (void)hipFree(L.cov); (void)hipFree(L.fcov); (void)hipFree(L.blocked);
+  (void)hipFree(L.rec); (void)hipFree(L.cov); (void)hipFree(L.blocked);
   if (L.burn_steps) (void)hipFree(L.burn_steps);
   L = LandscapeHost();
   for (auto &T : c->tg)

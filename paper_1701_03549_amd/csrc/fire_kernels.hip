@@ -39,6 +39,14 @@ struct Words4 {
   uint32_t v[4];
 };
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
+}
+
 __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1,
                                            uint32_t c2, uint32_t c3,
                                            uint32_t k0, uint32_t k1) {
@@ -48,9 +56,9 @@ __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1,
     const uint64_t p2 = (uint64_t)0xCD9E8D57u * c2;
     const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
     const uint32_t lo2 = (uint32_t)p2, hi2 = (uint32_t)(p2 >> 32);
-    c0 = hi2 ^ c1 ^ k0;
+    c0 = xor3(hi2, c1, k0);
     c1 = lo2;
-    c2 = hi0 ^ c3 ^ k1;
+    c2 = xor3(hi0, c3, k1);
     c3 = lo0;
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;
@@ -92,6 +100,15 @@ __device__ __forceinline__ double omega_of(float wind_deg, int d) {
 // threshold by one unit for about one x in 10^7. Beyond |x| = 40 the
 // quantised value is 0 or saturated already, so x is clamped there; a NaN
 // saturates.
+//
+// COMPACT: the series in a loop over a table, the same steps with a tenth of
+// the registers, for the rare evaluations of the simulation kernel (the
+// compiler keeps unrolled coefficients in registers throughout its step loop).
+__device__ __constant__ double kTaylor[13] = {
+    1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0,
+    1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.5, 1.0, 1.0};
+
+template <bool COMPACT = false>
 __device__ __forceinline__ uint32_t logistic_quantised(double x) {
   constexpr double kLog2e = 1.4426950408889634074;
   constexpr double kLn2Hi = 6.93147180369123816490e-01;
@@ -102,18 +119,23 @@ __device__ __forceinline__ uint32_t logistic_quantised(double x) {
   double r = fma(-n, kLn2Hi, -x);
   r = fma(-n, kLn2Lo, r);
   double e = 1.0 / 479001600.0;  // 1/12!
-  e = fma(e, r, 1.0 / 39916800.0);
-  e = fma(e, r, 1.0 / 3628800.0);
-  e = fma(e, r, 1.0 / 362880.0);
-  e = fma(e, r, 1.0 / 40320.0);
-  e = fma(e, r, 1.0 / 5040.0);
-  e = fma(e, r, 1.0 / 720.0);
-  e = fma(e, r, 1.0 / 120.0);
-  e = fma(e, r, 1.0 / 24.0);
-  e = fma(e, r, 1.0 / 6.0);
-  e = fma(e, r, 0.5);
-  e = fma(e, r, 1.0);
-  e = fma(e, r, 1.0);
+  if constexpr (COMPACT) {
+#pragma unroll 1
+    for (int i = 1; i < 13; ++i) e = fma(e, r, kTaylor[i]);
+  } else {
+    e = fma(e, r, 1.0 / 39916800.0);
+    e = fma(e, r, 1.0 / 3628800.0);
+    e = fma(e, r, 1.0 / 362880.0);
+    e = fma(e, r, 1.0 / 40320.0);
+    e = fma(e, r, 1.0 / 5040.0);
+    e = fma(e, r, 1.0 / 720.0);
+    e = fma(e, r, 1.0 / 120.0);
+    e = fma(e, r, 1.0 / 24.0);
+    e = fma(e, r, 1.0 / 6.0);
+    e = fma(e, r, 0.5);
+    e = fma(e, r, 1.0);
+    e = fma(e, r, 1.0);
+  }
   const double d = 1.0 + __builtin_amdgcn_ldexp(e, (int)n);
   double q = __builtin_amdgcn_rcp(d);
   q = fma(q, fma(-d, q, 1.0), q);
@@ -125,6 +147,7 @@ __device__ __forceinline__ uint32_t logistic_quantised(double x) {
   return nan || scaled >= 4294967295.0 ? kSaturated : t;
 }
 
+template <bool COMPACT = false>
 __device__ __forceinline__ uint32_t logistic_threshold(const double *beta, double i_f, double psi,
                                                        double omega, double sigma) {
   double x = beta[0];
@@ -132,19 +155,19 @@ __device__ __forceinline__ uint32_t logistic_threshold(const double *beta, doubl
   x = x + beta[2] * psi;
   x = x + beta[3] * omega;
   x = x + beta[4] * sigma;
-  return logistic_quantised(x);
+  return logistic_quantised<COMPACT>(x);
 }
 
 // The threshold from the landscape's precomputed covariates (F: pointer type
 // of the binary64 arrays).
-template <typename F>
+template <bool COMPACT = false, typename F>
 __device__ __forceinline__ uint32_t edge_threshold(const double *beta, uint32_t vu_t, F ps, F omega,
                                                    int64_t t, int d, uint32_t forest) {
   const uint32_t veg = vu_t & 0xFFu;
   if (veg == 0) return 0u;
   const bool up = ((vu_t >> (8 + d)) & 1u) != 0;
-  return logistic_threshold(beta, veg == forest ? 1.0 : 0.0, ps[2 * t], omega[8 * t + d],
-                            up ? ps[2 * t + 1] : 0.0);
+  return logistic_threshold<COMPACT>(beta, veg == forest ? 1.0 : 0.0, ps[2 * t], omega[8 * t + d],
+                                     up ? ps[2 * t + 1] : 0.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -172,7 +195,7 @@ __device__ __forceinline__ uint32_t edge_threshold(const double *beta, uint32_t 
 // went from 43.6 to 20.8 ms, 2000 fires on four lattices from 20.6 to
 // 10.2 ms.
 struct FilterBeta {
-  float b0, b01, b2, b3, b3r, b4;  // -log2(e) times b0, b0 + b1, b2, b3, b3 / sqrt 2, 2^-23 b4
+  float b0, b1, b2, b3, b3r, b4;  // -log2(e) times b0, b1, b2, b3, b3 / sqrt 2, 2^-23 b4
   float margin;
 };
 
@@ -181,7 +204,7 @@ __device__ __forceinline__ FilterBeta filter_beta(const double *beta) {
   constexpr double kSqrtHalf = 0.70710678118654752440;
   FilterBeta f;
   f.b0 = (float)(-kLog2e * beta[0]);
-  f.b01 = (float)(-kLog2e * (beta[0] + beta[1]));
+  f.b1 = (float)(-kLog2e * beta[1]);
   f.b2 = (float)(-kLog2e * beta[2]);
   f.b3 = (float)(-kLog2e * beta[3]);
   f.b3r = (float)(-kLog2e * kSqrtHalf * beta[3]);
@@ -204,10 +227,10 @@ __device__ __forceinline__ float exp2_fast(float x) {
 // mask, r the coin.
 __device__ __forceinline__ float coin_margin(const FilterBeta &f, float psi, uint32_t sfu, float wind,
                                              int d, uint32_t r) {
-  float x = (sfu & 256u) ? f.b01 : f.b0;
+  const uint32_t forest = 0u - ((sfu >> 8) & 1u), up = 0u - ((sfu >> d) & 1u);
+  float x = f.b0 + __uint_as_float(__float_as_uint(f.b1) & forest);
   x = fmaf(f.b2, psi, x);
   x = x + wind;
-  const uint32_t up = 0u - ((sfu >> d) & 1u);
   x = fmaf(f.b4, (float)((sfu >> 9) & up), x);
   const float u = fmaf((float)r, 0x1p-32f, 0x1p-33f);
   return fmaf(u, exp2_fast(x), u) - 1.0f;
@@ -377,18 +400,30 @@ __global__ void fill_u32_kernel(uint32_t *p, uint32_t v, int64_t n) {
 //   * the cells that ignited at the previous step form the frontier queue,
 //     entries x | y << 12 (the top byte is scratch), held in LDS up to
 //     queue_cap entries and in a per-workgroup global spill area beyond;
-//   * work is spread one lane per (frontier cell, group of four directions):
-//     the four edges of a group take their coins from the four words of one
-//     Philox call, which is most of the arithmetic of a step, so each call
-//     is made once; a lane reads its four thresholds with one 16-byte load;
+//   * a lane takes a frontier cell: its eight neighbours' bits are three reads
+//     of two adjacent words, its thresholds two 16-byte loads, and its coins
+//     the four words of each of two Philox calls (one per group of four
+//     directions), whose first rounds are shared. Fronts of at most half the
+//     workgroup take two lanes a cell, one group each: lanes are idle there and
+//     a step is one wave's instructions, one after another;
 //   * each step runs in two phases separated by barriers. Phase 1 only
 //     reads the bitset, so eligibility is judged against the burn state at
 //     the start of the step; it draws the coins of the eligible edges (small
-//     fronts keep the 4-bit outcome in registers, larger ones merge the two
-//     nibbles of a cell into its entry's top byte). Phase 2 sets the bits of
-//     the successful targets with atomic ORs; the lane whose OR flipped a bit
-//     owns that new cell and appends it to the next frontier (bit-sliced
+//     fronts keep the outcome in registers, larger ones put a cell's eight
+//     bits into its entry's top byte). Phase 2 sets the bits of the successful
+//     targets with atomic ORs, one or two a row; the lane whose OR flipped a
+//     bit owns that new cell and appends it to the next frontier (bit-sliced
 //     ballot prefix of the per-lane counts, one LDS atomic per wave).
+// A step of a small front is bound by one wave's chain of instructions
+// (gfx950, measured: 4 cycles a vector instruction, 28 where a scalar one
+// needs its result, 32 for an exec-masked region, 60 for a branch with a
+// store or an atomic, 82 an LDS atomic and 2 more for each further lane on
+// the same word), so its phases hold no branch per neighbour: stores and ORs
+// of nothing go to spare words instead. Against one lane per (cell, group)
+// with four reads and four atomics each, a branch per append and 625 VALU
+// instructions a step and simulation of the calibration batch (now 540): one fire at 512x512 279 -> 221 us, 1280 calibration fires 422 ->
+// 360 us, 32 fires across 1600x1600 46.3 -> 20.3 ms, 8192 Monte Carlo fires
+// (already with the coin filter) 20.8 -> 15.7 ms.
 // Every coin is a pure function of (sim_index, step, source cell, direction)
 // and ignition is an OR, so the burnt set, step count, trial count and
 // fitness do not depend on thread order or on the schedule.
@@ -413,6 +448,12 @@ typedef const __attribute__((address_space(1))) u32x4 gmem_cu32x4;
 
 // Four consecutive 32-bit words from a 16-byte aligned global address.
 __device__ __forceinline__ u32x4 load_x4(gmem_cu32 *q) { return *(gmem_cu32x4 *)q; }
+
+// The same at a byte offset (below 2^30: 32 bytes a cell of the largest
+// lattice) from a uniform base.
+__device__ __forceinline__ u32x4 load_x4_at(gmem_cu32 *base, uint32_t bytes) {
+  return *(gmem_cu32x4 *)((const __attribute__((address_space(1))) char *)base + bytes);
+}
 
 __device__ __forceinline__ uint4 load_rec(const uint4 *base, int64_t t) {
   gmem_cu32 *q = (gmem_cu32 *)(base + t);
@@ -454,11 +495,16 @@ constexpr int kRegRounds = 2;
 template <int BLOCK, bool TABLE, bool DUR, bool WIN, bool GB = false>
 __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
   static_assert(!(GB && WIN), "a global bitset covers the whole lattice");
+  // LDS: 15 control words (the last is never written: the word before the
+  // bitset, which may be read), the bitset, one word that takes what is not
+  // to be kept, the two queues, with DUR their life bytes
   extern __shared__ uint32_t lds[];
   const int bw = a.bitset_words;
   const uint32_t cap = (uint32_t)a.queue_cap;
-  uint32_t *const bits = GB ? a.gbits + (int64_t)blockIdx.x * bw : lds;
   const int lbw = GB ? 0 : bw;  // bitset words in LDS
+  uint32_t *const ctl = lds;
+  uint32_t *const bits = GB ? a.gbits + (int64_t)blockIdx.x * bw : lds + (kCtlWords - 1);
+  const uint32_t waste = (uint32_t)(kCtlWords - 1 + lbw), queues = waste + 1u;
   auto bload = [&](int w) -> uint32_t {
     if constexpr (GB) return __hip_atomic_load(&bits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else return bits[w];
@@ -472,12 +518,11 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
       return __hip_atomic_fetch_or(&bits[w], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else return atomicOr(&bits[w], v);
   };
-  uint32_t *const ctl = lds + lbw + 2 * cap;
   gmem_u32 *const spill_base = (gmem_u32 *)(a.ovf + (int64_t)blockIdx.x * 2 * a.ovf_cap);
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   // remaining active steps of the queue entries (DUR only)
-  uint8_t *const life_lds = reinterpret_cast<uint8_t *>(ctl + kCtlWords);
+  uint8_t *const life_lds = reinterpret_cast<uint8_t *>(lds + queues + 2 * cap);
   gmem_u8 *const life_spill =
       DUR ? (gmem_u8 *)(a.ovf_life + (int64_t)blockIdx.x * 2 * a.ovf_cap) : nullptr;
   auto l_load = [&](uint32_t q, uint32_t i) -> uint32_t {
@@ -491,11 +536,11 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
 
   // frontier queue q (0 or 1), entry i
   auto q_load = [&](uint32_t q, uint32_t i) -> uint32_t {
-    if (i < cap) return lds[lbw + q * cap + i];
+    if (i < cap) return lds[queues + q * cap + i];
     return spill_base[(int64_t)q * a.ovf_cap + (i - cap)];
   };
   auto q_store = [&](uint32_t q, uint32_t i, uint32_t v) {
-    if (i < cap) lds[lbw + q * cap + i] = v;
+    if (i < cap) lds[queues + q * cap + i] = v;
     else spill_base[(int64_t)q * a.ovf_cap + (i - cap)] = v;
   };
 
@@ -513,7 +558,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         a.times[2 * (int64_t)took] = wall_clock64();
     }
     __syncthreads();
-    const uint32_t sim = ctl[kSim];
+    const uint32_t sim = __builtin_amdgcn_readfirstlane(ctl[kSim]);
     if (sim == 0xFFFFFFFFu) break;
     const fire_sim sd = a.sims[sim];
 
@@ -600,8 +645,11 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
       return WIN && ((uint32_t)(x - x_lo) > x_span || (uint32_t)(y - y_lo) > y_span);
     };
     // LDS word of cell (x, y) inside the window
+    // (coordinates and row strides are below 2^12: a 24-bit product)
     const int w_off = wy0 * ws + wx0w;
-    auto bw_of = [&](int x, int y) -> int { return y * ws + (x >> 5) - w_off; };
+    auto bw_of = [&](int x, int y) -> int {
+      return (int)((uint32_t)(y & 0xFFF) * (uint32_t)(ws & 0xFFF)) + (x >> 5) - w_off;
+    };
     // global word of window word w
     auto gw_of = [&](int w) -> int { return (wy0 + w / ws) * stride + wx0w + w % ws; };
     const int wwords = wh * ws;
@@ -635,6 +683,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
 
     uint32_t cq = 0, step = 0;
     uint32_t my_trials = 0, my_new = 0;
+    uint32_t n_burnt = 0;  // one-step burns: cells of every frontier so far
     const uint32_t max_steps = sd.max_steps;
     const uint32_t sim_index = sd.sim_index;
     // frontier length of step k lives in ctl[kLen0 + k % 3]
@@ -649,245 +698,358 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         l_store(cq, i, life_of((int)(e & 0xFFFu), (int)((e >> 12) & 0xFFFu)));
     };
 
-    // The four edges of group g, k = 0..3, point to (0, -s), (s, -s),
-    // (s, 0), (s, s) with s = +1 for g = 0 (N, NE, E, SE) and s = -1 for
-    // g = 1 (S, SW, W, NW). Their LDS words and bits around a source at
-    // (x, y) with word `base` and bit xb: a column step crosses a word
-    // boundary only at bit 0 or 31.
-    struct GroupGeom {
-      int wk[4], bk[4];  // LDS word and bit of each target
-      int tk[4];         // lattice offset (cells) of each target
-      int s;
+    // The 3x3 neighbourhood of a cell in the bitset. A row of it is three
+    // bits from bit sh of the 64-bit pair (word w, word w + 1), w the word of
+    // the cell to the west; a row outside the bitset takes the cell's own.
+    // The pair may name the word before or after the bitset (a readable LDS
+    // word): bits taken from there, or from a neighbouring row, lie outside
+    // the lattice and are forced to 1.
+    struct Hood {
+      int w[3];
+      uint32_t sh;
     };
-    auto group_geom = [&](int xb, int base, uint32_t g) -> GroupGeom {
-      GroupGeom q;
-      q.s = g ? -1 : 1;
-      const int sws = g ? -ws : ws;
-      const int xs = xb + q.s;  // -1 .. 32
-      const int wo = xs >> 5;   // -1, 0 or 1
-      const int bs = xs & 31;
-      q.wk[0] = base - sws;      q.bk[0] = xb;
-      q.wk[1] = base - sws + wo; q.bk[1] = bs;
-      q.wk[2] = base + wo;       q.bk[2] = bs;
-      q.wk[3] = base + sws + wo; q.bk[3] = bs;
-      const int sW = g ? -W : W;
-      q.tk[0] = -sW;
-      q.tk[1] = q.s - sW;
-      q.tk[2] = q.s;
-      q.tk[3] = q.s + sW;
-      return q;
+    const int x_first = 32 * wx0w, y_last = wy0 + wh - 1;
+    auto hood = [&](int x, int y) -> Hood {
+      Hood h;
+      h.sh = (uint32_t)(x - 1) & 31u;
+      const int lo = bw_of(x, y) - ((x & 31) == 0 ? 1 : 0);
+      h.w[0] = lo - (y > wy0 ? ws : 0);
+      h.w[1] = lo;
+      h.w[2] = lo + (y < y_last ? ws : 0);
+      return h;
     };
-
-    // Phase 1 for one unit: frontier entry e and direction group g (edges
-    // d = 4g .. 4g+3, whose coins are the four words of one Philox call
-    // (sim_index, step, source, g)). An edge is tried when its target is
-    // inside, burnable and unburnt at the start of the step. Returns the
-    // 4-bit mask of tried edges whose coin succeeds; n_tried counts the
-    // tried edges.
-    auto unit_outcome = [&](uint32_t e, uint32_t g, uint32_t &n_tried) -> uint32_t {
-      const int x = (int)(e & 0xFFFu), y = (int)((e >> 12) & 0xFFFu);
-      const uint32_t s_lin = (uint32_t)(y * W + x);
-      // a source at a window edge: read none of its neighbours; bit 4 of
-      // the result asks phase 2 to end the run
-      const bool edge = near_edge(x, y);
-      uint32_t thr[4] = {0u, 0u, 0u, 0u};
-      if (TABLE) {
-        // the 8 thresholds of a source are 32 contiguous bytes; group g is
-        // the 16-byte half g (tables are 16-byte aligned)
-        const u32x4 t4 = load_x4(table + (int64_t)s_lin * 8 + 4 * g);
-        thr[0] = t4.x; thr[1] = t4.y; thr[2] = t4.z; thr[3] = t4.w;
-      }
-      // neighbour words from the source's: one row is ws words, and a
-      // column step crosses a word boundary only at bit 0 or 31. An edge
-      // whose target is outside (or whose source is at a window edge) reads
-      // the source's own bit, which is set: the four reads are unconditional
-      // and issue back to back.
-      const int base = bw_of(x, y), xb = x & 31;
-      const GroupGeom q = group_geom(xb, base, g);
-      const bool r1 = (unsigned)(y - q.s) < (unsigned)H && !edge;  // row -s
-      const bool r2 = (unsigned)(y + q.s) < (unsigned)H && !edge;  // row +s
-      const bool c1 = (unsigned)(x + q.s) < (unsigned)W;           // column +s
-      const bool in[4] = {r1, r1 && c1, c1 && !edge, r2 && c1};
-      uint32_t elig = 0;
+    auto pair_bits = [](uint32_t lo, uint32_t hi, uint32_t sh) -> uint32_t {
+#ifdef __HIP_DEVICE_COMPILE__
+      return __builtin_amdgcn_alignbit(hi, lo, sh);
+#else
+      return (uint32_t)((((uint64_t)hi << 32) | lo) >> (sh & 31u));
+#endif
+    };
+    // the neighbourhood's clear bits (cells that may ignite): 0..2 the row
+    // above (west to east), 3 and 5 the cell's own row, 6..8 the row below
+    auto hood_clear = [&](const Hood &h, int x, int y) -> uint32_t {
+      uint32_t lo[3], hi[3];
+      if constexpr (GB) {
+        // the second word only where the three bits reach it (it need not
+        // exist otherwise)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int w = in[k] ? q.wk[k] : base;
-        const int b = in[k] ? q.bk[k] : xb;
-        elig |= ((bload(w) >> b) & 1u) == 0 ? (1u << k) : 0u;
-      }
-      n_tried = __popc(elig);
-      // not gated on elig: the rounds then overlap the bitset and table reads
-      const Words4 r = philox10(sim_index, step, s_lin, g, a.key0, a.key1);
-      uint32_t hit = 0;
-      if (TABLE) {
+        for (int r = 0; r < 3; ++r) {
+          lo[r] = bload(max(h.w[r], 0));
+          hi[r] = 0u;
+        }
+        if (h.sh == 31u || (h.sh == 30u && x + 1 < W)) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (((elig >> k) & 1u) && (thr[k] == kSaturated || r.v[k] < thr[k])) hit |= 1u << k;
+          for (int r = 0; r < 3; ++r) hi[r] = bload(h.w[r] + 1);
+        }
       } else {
-        // the filter covariates of all four targets are read first (an
-        // ineligible edge reads its source's own)
-        u32x4 c[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t t = ((elig >> k) & 1u) ? s_lin + (uint32_t)q.tk[k] : s_lin;
-          c[k] = load_x4((gmem_cu32 *)L.fcov + (int64_t)t * 4);
-        }
-        const float b3 = g ? -fbeta.b3 : fbeta.b3, b3r = g ? -fbeta.b3r : fbeta.b3r;
-        uint32_t unsure = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float cw = __uint_as_float(c[k].z), sw = __uint_as_float(c[k].w);
-          const float wind = k == 0 ? b3 * cw : k == 1 ? b3r * (cw + sw) : k == 2 ? b3 * sw
-                                                                          : b3r * (sw - cw);
-          const float m = coin_margin(fbeta, __uint_as_float(c[k].x), c[k].y, wind,
-                                      4 * (int)g + k, r.v[k]);
-          hit |= m < -fbeta.margin ? 1u << k : 0u;
-          unsure |= !(fabsf(m) > fbeta.margin) ? 1u << k : 0u;
-        }
-        hit &= elig;
-        unsure &= elig;
-        while (unsure) {
-          const int k = __builtin_ctz(unsure);
-          unsure &= unsure - 1u;
-          double beta[5];
-          for (int i = 0; i < 5; ++i) beta[i] = ((gmem_cf64 *)bp)[i];
-          const int64_t tl = (int64_t)s_lin + (k == 0 ? q.tk[0] : k == 1 ? q.tk[1] : k == 2 ? q.tk[2] : q.tk[3]);
-          const uint32_t t = edge_threshold(beta, rec_word(L.rec, tl), (gmem_cf64 *)L.ps,
-                                            (gmem_cf64 *)L.omega, tl, 4 * (int)g + k, L.forest_class);
-          const uint32_t coin = k == 0 ? r.v[0] : k == 1 ? r.v[1] : k == 2 ? r.v[2] : r.v[3];
-          if (t == kSaturated || coin < t) hit |= 1u << k;
+        for (int r = 0; r < 3; ++r) {
+          lo[r] = bits[h.w[r]];
+          hi[r] = bits[h.w[r] + 1];
         }
       }
-      return hit | (WIN && edge ? 16u : 0u);
+      // what lies outside the lattice: the columns to the west and east, the
+      // rows above and below
+      uint32_t open = 0x1EFu;
+      if (x == x_first) open &= ~0x49u;
+      if (x == W - 1) open &= ~0x124u;
+      if (y == wy0) open &= ~0x7u;
+      if (y == y_last) open &= ~0x1C0u;
+      const uint32_t set = (pair_bits(lo[0], hi[0], h.sh) & 7u) | ((pair_bits(lo[1], hi[1], h.sh) & 7u) << 3) |
+                           (pair_bits(lo[2], hi[2], h.sh) << 6);
+      return ~set & open;
+    };
+    // The edges of group g = 0 (N, NE, E, SE) are the neighbourhood bits
+    // 1, 2, 5 and 8; those of g = 1 (S, SW, W, NW) the same bits of the
+    // neighbourhood turned by 180 degrees.
+    constexpr uint32_t kGroupBit[4] = {2u, 4u, 32u, 256u};
+    auto turn = [](uint32_t bits, uint32_t g) -> uint32_t {
+      return g ? __builtin_bitreverse32(bits) >> 23 : bits;
     };
 
-    // Phase 2 for one unit: set the bits of the hit targets; returns the
-    // mask of targets whose bit this lane flipped (cells it now owns).
-    auto unit_ignite = [&](uint32_t e, uint32_t g, uint32_t hit) -> uint32_t {
-      uint32_t fresh = 0;
+    // Phase 1 for one cell: frontier entry e. The coins of group g's edges
+    // are the four words of the Philox call (sim_index, step, source, g). An
+    // edge is tried when its target is inside, burnable and unburnt at the
+    // start of the step. Returns the neighbourhood bits of the tried edges
+    // whose coin succeeds; kEdge asks phase 2 to end the run (the source is
+    // at a window edge; none of its neighbours is read). `one`: only the
+    // group `only`, else both.
+    constexpr uint32_t kEdge = 512u;
+    auto cell_outcome = [&](auto one, uint32_t only, uint32_t e, Hood &h) -> uint32_t {
+      constexpr int kGroups = decltype(one)::value ? 1 : 2;
       const int x = (int)(e & 0xFFFu), y = (int)((e >> 12) & 0xFFFu);
-      // branch-free: an edge that did not hit ORs 0 into its source's own
-      // word, so the four atomics issue back to back
-      const int base = bw_of(x, y), xb = x & 31;
-      const GroupGeom q = group_geom(xb, base, g);
-      uint32_t old[4], bitv[4];
+      const uint32_t s_lin = (uint32_t)y * (uint32_t)(W & 0x1FFF) + (uint32_t)x;
+      const bool edge = near_edge(x, y);
+      u32x4 thr[kGroups];
+      if (TABLE) {
+        // the 8 thresholds of a source are 32 contiguous bytes, group g the
+        // 16-byte half g (tables are 16-byte aligned)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const bool h = (hit >> k) & 1u;
-        const int w = h ? q.wk[k] : base;
-        bitv[k] = h ? 1u << q.bk[k] : 0u;
-        old[k] = bor(w, bitv[k]);
+        for (int i = 0; i < kGroups; ++i)
+          thr[i] = load_x4(table + (s_lin * 8u + 4u * (kGroups == 1 ? only : (uint32_t)i)));
       }
+      h = hood(x, y);
+      uint32_t elig = hood_clear(h, x, y);
+      if (edge) elig = 0u;
+      uint32_t hit = 0;
+      auto group = [&](uint32_t g, int i) {
+        const uint32_t el = turn(elig, g) & 0x126u;
+        my_trials += __popc(el);
+        uint32_t hg = 0;
+        // not gated on el: the rounds then overlap the bitset and table reads
+        const Words4 r = philox10(sim_index, step, s_lin, g, a.key0, a.key1);
+        if (TABLE) {
+          const uint32_t t[4] = {thr[i].x, thr[i].y, thr[i].z, thr[i].w};
+          // r < T, or T saturated (2^32 - 1, above every capped word)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (bitv[k] && (old[k] & bitv[k]) == 0) fresh |= 1u << k;
+          for (int k = 0; k < 4; ++k)
+            hg |= min(r.v[k], kSaturated - 1u) < t[k] ? kGroupBit[k] : 0u;
+          hg &= el;
+        } else {
+          // the filter covariates of the four targets are read first (an
+          // ineligible edge reads its source's own): (0, -s), (s, -s),
+          // (s, 0), (s, s) with s = +1 for g = 0 and -1 for g = 1
+          const int s = g ? -1 : 1;
+          const int tk[4] = {-s * W, s - s * W, s, s + s * W};
+          u32x4 c[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t t = (el & kGroupBit[k]) ? s_lin + (uint32_t)tk[k] : s_lin;
+            c[k] = load_x4_at((gmem_cu32 *)L.fcov, t * 16u);
+          }
+          const float b3 = g ? -fbeta.b3 : fbeta.b3, b3r = g ? -fbeta.b3r : fbeta.b3r;
+          uint32_t unsure = 0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float cw = __uint_as_float(c[k].z), sw = __uint_as_float(c[k].w);
+            const float wind = k == 0 ? b3 * cw : k == 1 ? b3r * (cw + sw) : k == 2 ? b3 * sw
+                                                                            : b3r * (sw - cw);
+            const float m = coin_margin(fbeta, __uint_as_float(c[k].x), c[k].y, wind, 4 * (int)g + k,
+                                        r.v[k]);
+            hg |= m < -fbeta.margin ? kGroupBit[k] : 0u;
+            unsure |= !(fabsf(m) > fbeta.margin) ? kGroupBit[k] : 0u;
+          }
+          hg &= el;
+          unsure &= el;
+          while (unsure) {
+            // within the margin: the binary64 threshold (and the coin drawn
+            // again, so that no word is held for this rare case)
+            const uint32_t bit = unsure & (0u - unsure);
+            unsure ^= bit;
+            const int k = bit == 2u ? 0 : bit == 4u ? 1 : bit == 32u ? 2 : 3;
+            const Words4 q = philox10(sim_index, step, s_lin, g, a.key0, a.key1);
+            const uint32_t coin = k & 2 ? (k & 1 ? q.v[3] : q.v[2]) : (k & 1 ? q.v[1] : q.v[0]);
+            gmem_cf64 *const b = (gmem_cf64 *)bp;
+            const double beta[5] = {b[0], b[1], b[2], b[3], b[4]};
+            const int64_t tl = (int64_t)s_lin + s * (k == 0 ? -W : k == 1 ? 1 - W : k == 2 ? 1 : 1 + W);
+            const uint32_t t =
+                edge_threshold<true>(beta, rec_word(L.rec, tl), (gmem_cf64 *)L.ps,
+                                     (gmem_cf64 *)L.omega, tl, 4 * (int)g + k, L.forest_class);
+            if (t == kSaturated || coin < t) hg |= bit;
+          }
+        }
+        hit |= turn(hg, g);
+      };
+      if constexpr (kGroups == 1) {
+        group(only, 0);
+      } else {
+        group(0u, 0);
+        group(1u, 1);
+      }
+      return hit | (WIN && edge ? kEdge : 0u);
+    };
+
+    // Phase 2 for one cell: set the bits of the hit targets, one atomic OR a
+    // row and one in the next word where the row's bits cross it; returns
+    // the neighbourhood bits this lane flipped (cells it now owns). In LDS
+    // all six are issued without a branch (about 60 cycles each to a wave);
+    // an OR of nothing goes to an entry of the current queue, another one for
+    // each lane (lanes on one word are served in turn).
+    auto cell_ignite = [&](const Hood &h, uint32_t hit) -> uint32_t {
+      uint32_t lo[3], hi[3], old_lo[3], old_hi[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const uint64_t m = (uint64_t)((hit >> (3 * r)) & 7u) << h.sh;
+        lo[r] = (uint32_t)m;
+        hi[r] = (uint32_t)(m >> 32);
+        old_lo[r] = old_hi[r] = 0xFFFFFFFFu;
+      }
+      if constexpr (GB) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          if (lo[r]) old_lo[r] = bor(h.w[r], lo[r]);
+        if (hi[0] | hi[1] | hi[2]) {
+#pragma unroll
+          for (int r = 0; r < 3; ++r)
+            if (hi[r]) old_hi[r] = bor(h.w[r] + 1, hi[r]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          const uint32_t w = (uint32_t)(h.w[r] + kCtlWords - 1);
+          const uint32_t idle = queues + cq * cap + min((uint32_t)tid, cap - 1);
+          old_lo[r] = atomicOr(&lds[lo[r] ? w : idle], lo[r]);
+          old_hi[r] = atomicOr(&lds[hi[r] ? w + 1u : idle], hi[r]);
+        }
+      }
+      uint32_t fresh = 0;
+#pragma unroll
+      for (int r = 0; r < 3; ++r)
+        fresh |= (pair_bits(lo[r] & ~old_lo[r], hi[r] & ~old_hi[r], h.sh) & 7u) << (3 * r);
       return fresh;
     };
 
-    // Append each lane's fresh cells to the next frontier: a wave-wide
-    // exclusive prefix of the per-lane counts (0..4) from three bit-sliced
-    // ballots, one LDS atomic per wave. `direct`: the queue slot is known to
-    // lie in LDS.
-    auto append = [&](uint32_t e, uint32_t g, uint32_t fresh, int nslot, bool direct) {
+    // Append each lane's cells, the neighbourhood bits `fresh` of entry e, to
+    // the next frontier: a wave-wide exclusive prefix of the per-lane counts
+    // from bit-sliced ballots, one LDS atomic a wave (none if `solo`: no
+    // other wave appends in this step). `one`: the cells are of group g only
+    // (at most 4). Called by whole waves. Slots in LDS are stored without
+    // branches, what is not fresh to the waste word: a branch per neighbour
+    // costs a wave about 60 cycles, the store to one word nothing.
+    auto append = [&](auto one, uint32_t g, uint32_t e, uint32_t fresh, int nslot, bool solo) {
+      constexpr bool kOne = decltype(one)::value;
       const uint32_t cnt = __popc(fresh);
       const uint64_t b0 = __ballot(cnt & 1u), b1 = __ballot(cnt & 2u), b2 = __ballot(cnt & 4u);
-      const uint32_t total = (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
+      uint32_t total = (uint32_t)(__popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2));
+      uint32_t idx = lane_prefix(b0) + 2 * lane_prefix(b1) + 4 * lane_prefix(b2);
+      if (!kOne) {
+        const uint64_t b3 = __ballot(cnt & 8u);
+        total += 8 * (uint32_t)__popcll(b3);
+        idx += 8 * lane_prefix(b3);
+      }
       if (total == 0) return;
       uint32_t wbase = 0;
-      if (lane == 0) wbase = atomicAdd(&ctl[kLen0 + nslot], total);
-      wbase = __builtin_amdgcn_readfirstlane(wbase);
-      if (!fresh) return;
-      uint32_t idx = wbase + lane_prefix(b0) + 2 * lane_prefix(b1) + 4 * lane_prefix(b2);
-      const int x = (int)(e & 0xFFFu), y = (int)((e >> 12) & 0xFFFu);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (!((fresh >> k) & 1u)) continue;
-        // edge k of group g: (0, -s), (s, -s), (s, 0), (s, s)
-        const int sg = g ? -1 : 1;
-        const int tx = x + (k == 0 ? 0 : sg), ty = y + (k == 2 ? 0 : (k == 3 ? sg : -sg));
-        const uint32_t v = (uint32_t)tx | ((uint32_t)ty << 12);
-        if (direct) {
-          lds[lbw + (cq ^ 1u) * cap + idx] = v;
-          if (DUR) life_lds[(cq ^ 1u) * cap + idx] = 0u;
-        } else {
-          q_store(cq ^ 1u, idx, v);
-          if (DUR) l_store(cq ^ 1u, idx, 0u);
+      if (solo) {
+        ctl[kLen0 + nslot] = total;
+      } else {
+        if (lane == 0) {
+          // the slot is hidden from the compiler, which would otherwise wrap
+          // the one lane's addition in a wave-wide one
+          uint32_t at = kLen0 + (uint32_t)nslot;
+#ifdef __HIP_DEVICE_COMPILE__
+          asm volatile("" : "+v"(at));
+#endif
+          wbase = atomicAdd(&ctl[at], total);
         }
-        ++idx;
-        ++my_new;
+        wbase = __builtin_amdgcn_readfirstlane(wbase);
+      }
+      idx += wbase;
+      if (DUR) my_new += cnt;
+      const uint32_t cell = e & 0xFFFFFFu;
+      if (wbase + total <= cap) {
+        const uint32_t q = (cq ^ 1u) * cap + idx;
+        const uint32_t f = kOne ? turn(fresh, g) : fresh;
+        const int s = kOne && g ? -1 : 1;
+#pragma unroll
+        for (int b = 0; b < 9; ++b) {
+          if (b == 4 || (kOne && ((0x126u >> b) & 1u) == 0)) continue;
+          const uint32_t slot_b = q + __popc(f & ((1u << b) - 1u));
+          const bool own = (f >> b) & 1u;
+          lds[own ? queues + slot_b : waste] =
+              cell + (uint32_t)(s * ((b % 3 - 1) + ((b / 3 - 1) * 4096)));
+          if (DUR)
+            reinterpret_cast<uint8_t *>(lds)[own ? 4u * (queues + 2u * cap) + slot_b : 4u * waste] = 0u;
+        }
+      } else {
+        while (fresh) {
+          const int b = __builtin_ctz(fresh), row = (b * 11) >> 5;
+          fresh &= fresh - 1u;
+          q_store(cq ^ 1u, idx, cell + (uint32_t)((b - 3 * row - 1) + ((row - 1) * 4096)));
+          if (DUR) l_store(cq ^ 1u, idx, 0u);
+          ++idx;
+        }
       }
     };
 
+    // the first thread of this wave (wave-uniform)
+    const int wave_first = __builtin_amdgcn_readfirstlane(tid);
+
     for (;; ++step) {
       // the frontier length and this lane's first entry are read together
-      const uint32_t n_cur = ctl[kLen0 + slot];
-      const uint32_t e_first = lds[lbw + cq * cap + min((uint32_t)tid >> 1, cap - 1)];
+      const uint32_t n_read = ctl[kLen0 + slot];
+      const uint32_t e_first = lds[queues + cq * cap + min((uint32_t)tid >> 1, cap - 1)];
+      const uint32_t n_cur = __builtin_amdgcn_readfirstlane(n_read);
       aborted = WIN && ctl[kAbort0 + slot] != 0u;
+      if (!DUR) n_burnt += n_cur;
       if (n_cur == 0 || step >= max_steps || aborted) break;
       const int nslot = slot == 2 ? 0 : slot + 1;
-      if (tid == 0) {
-        ctl[kLen0 + nslot] = 0;
-        if (WIN) ctl[kAbort0 + nslot] = 0;
-      }
-      const uint32_t n_units = 2 * n_cur;
+      // (every lane stores: stores to one word cost what one costs)
+      ctl[kLen0 + nslot] = 0;
+      if (WIN) ctl[kAbort0 + nslot] = 0;
+      // an edge cell's store to the abort flag, to the waste word from others
+      auto flag_edge = [&](uint32_t hit) {
+        if (WIN) lds[(hit & kEdge) ? kAbort0 + (uint32_t)nslot : waste] = 1u;
+      };
 
-      if (n_units <= (uint32_t)(kRegRounds * BLOCK) && n_cur <= cap) {
-        // -- small front: outcomes stay in registers between the phases and
-        //    the current queue is in LDS; new cells go straight to LDS when
-        //    they cannot outgrow it (8 per entry), else through q_store --
-        const bool direct = 8 * n_cur <= cap;
+      if (2 * n_cur <= (uint32_t)BLOCK && n_cur <= cap) {
+        // -- smallest fronts: two lanes a cell, one group each, which halves
+        //    a lane's instructions where lanes are idle anyway ------------
+        const uint32_t g = (uint32_t)tid & 1u;
+        uint32_t hit = 0;
+        Hood h{};
+        if ((uint32_t)tid < 2 * n_cur) {
+          if (g == 0) resolve_life(e_first, (uint32_t)tid >> 1);
+          hit = cell_outcome(std::true_type{}, g, e_first, h);
+        }
+        __syncthreads();
+        // (waves without a cell have nothing to add)
+        if ((uint32_t)wave_first < 2 * n_cur) {
+          flag_edge(hit);
+          hit &= 0x1FFu;
+          const uint32_t fresh = cell_ignite(h, hit);
+          append(std::true_type{}, g, e_first, fresh, nslot, 2 * n_cur <= 64u);
+        }
+      } else if (n_cur <= (uint32_t)(kRegRounds * BLOCK) && n_cur <= cap) {
+        // -- small fronts: a lane a cell, outcomes stay in registers between
+        //    the phases and the current queue is in LDS ------------------
         uint32_t hit[kRegRounds], ent[kRegRounds];
+        Hood h[kRegRounds];
 #pragma unroll
         for (int rr = 0; rr < kRegRounds; ++rr) {
           hit[rr] = 0;
           ent[rr] = 0;
-          const uint32_t j = (uint32_t)(tid + rr * BLOCK);
-          if (rr * BLOCK < (int)n_units && j < n_units) {
-            const uint32_t e = rr == 0 ? e_first : lds[lbw + cq * cap + (j >> 1)];
+          h[rr] = Hood{};
+          const uint32_t i = (uint32_t)(tid + rr * BLOCK);
+          if (rr * BLOCK < (int)n_cur && i < n_cur) {
+            const uint32_t e = lds[queues + cq * cap + i];
             ent[rr] = e;
-            if ((j & 1u) == 0) resolve_life(e, j >> 1);
-            uint32_t nt;
-            hit[rr] = unit_outcome(e, j & 1u, nt);
-            my_trials += nt;
+            resolve_life(e, i);
+            hit[rr] = cell_outcome(std::false_type{}, 0u, e, h[rr]);
           }
         }
         __syncthreads();
 #pragma unroll
         for (int rr = 0; rr < kRegRounds; ++rr) {
-          if (rr * BLOCK >= (int)n_units) break;
-          const uint32_t g = (uint32_t)tid & 1u;
-          if (WIN && (hit[rr] & 16u)) ctl[kAbort0 + nslot] = 1u;
-          const uint32_t h4 = hit[rr] & 15u;
-          const uint32_t fresh = h4 ? unit_ignite(ent[rr], g, h4) : 0u;
-          append(ent[rr], g, fresh, nslot, direct);
+          if (wave_first + rr * BLOCK >= (int)n_cur) break;
+          flag_edge(hit[rr]);
+          const uint32_t fresh = cell_ignite(h[rr], hit[rr] & 0x1FFu);
+          append(std::false_type{}, 0u, ent[rr], fresh, nslot, n_cur <= 64u);
         }
       } else {
-        // -- general front: the two units of an entry merge their outcome
-        //    nibbles into the entry's top byte; queues spill to global
-        //    memory past queue_cap ----------------------------------------
-        for (uint32_t j = tid; j < n_units; j += BLOCK) {
-          const uint32_t e = q_load(cq, j >> 1);
-          if ((j & 1u) == 0) resolve_life(e, j >> 1);
-          uint32_t nt;
-          const uint32_t m = unit_outcome(e, j & 1u, nt) & 15u;
-          my_trials += nt;
-          const uint32_t other = (uint32_t)__shfl_xor((int)m, 1);
-          const uint32_t m8 = (j & 1u) ? 0u : (m | (other << 4));
-          if (m8 != 0) q_store(cq, j >> 1, e | (m8 << 24));
+        // -- general front: a cell's hits (its eight neighbours, the center
+        //    bit left out) wait in its entry's top byte; queues spill to
+        //    global memory past queue_cap --------------------------------
+        for (uint32_t i = tid; i < n_cur; i += BLOCK) {
+          const uint32_t e = q_load(cq, i);
+          resolve_life(e, i);
+          Hood h;
+          const uint32_t m = cell_outcome(std::false_type{}, 0u, e, h);
+          const uint32_t m8 = (m & 15u) | ((m >> 1) & 0xF0u);
+          if (m8 != 0) q_store(cq, i, e | (m8 << 24));
         }
         __syncthreads();
-        for (uint32_t base = 0; base < n_units; base += BLOCK) {
-          const uint32_t j = base + (uint32_t)tid;
-          const uint32_t g = j & 1u;
+        for (uint32_t base = 0; base < n_cur; base += BLOCK) {
+          const uint32_t i = base + (uint32_t)tid;
           uint32_t e = 0, fresh = 0;
-          if (j < n_units) {
-            e = q_load(cq, j >> 1);
-            if (WIN && near_edge((int)(e & 0xFFFu), (int)((e >> 12) & 0xFFFu)))
-              ctl[kAbort0 + nslot] = 1u;
-            const uint32_t hit = (e >> (24 + 4 * g)) & 0xFu;
-            if (hit) fresh = unit_ignite(e, g, hit);
+          if (i < n_cur) {
+            e = q_load(cq, i);
+            const int x = (int)(e & 0xFFFu), y = (int)((e >> 12) & 0xFFFu);
+            if (WIN && near_edge(x, y)) ctl[kAbort0 + nslot] = 1u;
+            const uint32_t m8 = e >> 24;
+            const uint32_t hit = (m8 & 15u) | ((m8 & 0xF0u) << 1);
+            if (hit) fresh = cell_ignite(hood(x, y), hit);
           }
-          append(e, g, fresh, nslot, false);
+          append(std::false_type{}, 0u, e, fresh, nslot, false);
         }
       }
       if (DUR) {
@@ -929,7 +1091,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
 
     // -- result: counts, Eq. 2 over the rows the fire reached, map ---------
     if (my_trials) atomicAdd(&ctl[kTrials], my_trials);
-    if (my_new) atomicAdd(&ctl[kNew], my_new);
+    if (DUR && my_new) atomicAdd(&ctl[kNew], my_new);
     __syncthreads();
     if (has_target) {
       // |A n A*| = popcount(burnt & reference) over the bitset
@@ -944,7 +1106,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
     }
     if (tid == 0) {
       fire_result r;
-      r.burnt = 1u + ctl[kNew];
+      r.burnt = DUR ? 1u + ctl[kNew] : n_burnt;
       r.steps = step;
       r.trials = ctl[kTrials];
       if (has_target) {

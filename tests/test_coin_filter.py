@@ -24,7 +24,6 @@ def _filter(beta, forest, psi, wind_deg, slope, up, d, r, ulp):
     """coin_margin and filter_beta in numpy: (s, margin); ulp scales 2^x by
     1 + ulp * 2^-23 (the instruction's last place)."""
     b = [(-LOG2E * beta[:, i]).astype(F) for i in range(5)]
-    b01 = (-LOG2E * (beta[:, 0] + beta[:, 1])).astype(F)
     b3r = (-LOG2E * np.sqrt(0.5) * beta[:, 3]).astype(F)
     b4 = (-LOG2E / 8388608.0 * beta[:, 4]).astype(F)
     rad = np.deg2rad(wind_deg.astype(np.float64))
@@ -32,7 +31,7 @@ def _filter(beta, forest, psi, wind_deg, slope, up, d, r, ulp):
     s4 = np.where(d < 4, F(1), F(-1))
     wind = np.select([d % 4 == 0, d % 4 == 1, d % 4 == 2], [s4 * b[3] * cw, s4 * b3r * (cw + sw), s4 * b[3] * sw],
                      s4 * b3r * (sw - cw)).astype(F)
-    x = np.where(forest, b01, b[0])
+    x = b[0] + np.where(forest, b[1], F(0))
     x = _fma(b[2], psi.astype(F), x) + wind
     x = _fma(b4, np.where(up, np.rint(slope * 8388608.0), 0.0).astype(F), x)
     u = _fma(r.astype(F), F(2.0 ** -32), F(2.0 ** -33))

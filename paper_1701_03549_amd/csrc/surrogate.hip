@@ -216,7 +216,144 @@ hipError_t gemm(int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak
 }
 
 // ---------------------------------------------------------------------------
+// The MLP's forward pass in one launch: a workgroup of 8 waves takes 32 rows
+// through all layers, activations in LDS, wave w computing columns 32 w ..
+// 32 w + 31 of each layer with 32x32x16 MFMAs in ascending k (the sums of
+// gemm_kernel, bit for bit). The weights are read from their transposed bf16
+// copy `wt` (fire_nn), whose rows hold a lane's 8 consecutive k in one 16-byte
+// load; all of a layer's loads are in flight before its first MFMA, and a
+// layer's begin before the previous one's barrier. What bounds it is that
+// chain of three layers (load latency, 16 dependent MFMAs, two barriers) and
+// the launch: a scoring call of 498 rows takes 12.5 us, against 39.8 us for
+// five launches of 8 to 32 workgroups and a copy.
+constexpr int kMlpH = 256, kMlpIn = 16, kMlpRows = 32, kMlpLd = kMlpH + 8;
+constexpr int kMlpThreads = 512;
+
+// acc += act[32][K] times the wave's 32 columns of w ([256][K] transposed
+// weights, w at the wave's first column's row)
+template <int K>
+__device__ __forceinline__ void mlp_load(const uint16_t *w, int lane, uint4 (&b)[K / 16]) {
+#pragma unroll
+  for (int s = 0; s < K / 16; ++s)
+    b[s] = *reinterpret_cast<const uint4 *>(w + (lane & 31) * K + 16 * s + 8 * (lane >> 5));
+}
+
+template <int K>
+__device__ __forceinline__ f32x16_t mlp_tile(const uint16_t *act, int lane, const uint4 (&b)[K / 16]) {
+  f32x16_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+#pragma unroll
+  for (int s = 0; s < K / 16; ++s) {
+    const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(&act[(lane & 31) * kMlpLd + 16 * s + 8 * (lane >> 5)]);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, b[s]), acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+__global__ __launch_bounds__(kMlpThreads) void mlp_forward_kernel(
+    const float *x, int B, float inv_w, float inv_h, const uint16_t *w1t, const uint16_t *w2t,
+    const uint16_t *w3t, const uint16_t *wf, const float *c1, const float *c2, const float *c3,
+    const float *cf, uint16_t *xb, uint16_t *h1b, uint16_t *h2b, uint16_t *h3b, float *t) {
+  __shared__ __attribute__((aligned(16))) uint16_t act[2][kMlpRows * kMlpLd];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = blockIdx.x * kMlpRows, col = 32 * wave + (lane & 31);
+  uint4 b1[1], b2[16];
+  mlp_load<kMlpIn>(w1t + 32 * wave * kMlpIn, lane, b1);
+  mlp_load<kMlpH>(w2t + 32 * wave * kMlpH, lane, b2);
+  {
+    // the inputs: beta / 30, ignition scaled to [-1, 1], zero padding
+    const int r = tid >> 4, k = tid & 15, b = row0 + r;
+    float v = 0.0f;
+    if (b < B) {
+      if (k < 5) v = x[b * 7 + k] * (1.0f / 30.0f);
+      else if (k == 5) v = 2.0f * x[b * 7 + 5] * inv_w - 1.0f;
+      else if (k == 6) v = 2.0f * x[b * 7 + 6] * inv_h - 1.0f;
+    }
+    const uint16_t q = f2bf(v);
+    act[0][r * kMlpLd + k] = q;
+    if (xb && b < B) xb[(int64_t)b * kMlpIn + k] = q;
+  }
+  __syncthreads();
+  // a layer's outputs: bias, ReLU, bf16, into the next layer's buffer
+  auto finish = [&](const f32x16_t &acc, const float *bias, uint16_t *to) {
+    const float bc = bias[col];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int i = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      to[i * kMlpLd + col] = f2bf(fmaxf(acc[v] + bc, 0.0f));
+    }
+  };
+  // the workgroup's rows of a layer to global memory
+  auto keep = [&](const uint16_t *from, uint16_t *h) {
+    if (!h) return;
+    for (int i = tid; i < kMlpRows * (kMlpH / 8); i += kMlpThreads) {
+      const int r = i / (kMlpH / 8), k = (i % (kMlpH / 8)) * 8;
+      if (row0 + r < B)
+        *reinterpret_cast<uint4 *>(h + (int64_t)(row0 + r) * kMlpH + k) =
+            *reinterpret_cast<const uint4 *>(&from[r * kMlpLd + k]);
+    }
+  };
+  finish(mlp_tile<kMlpIn>(act[0], lane, b1), c1, act[1]);
+  __syncthreads();
+  keep(act[1], h1b);
+  const f32x16_t a2 = mlp_tile<kMlpH>(act[1], lane, b2);
+  mlp_load<kMlpH>(w3t + 32 * wave * kMlpH, lane, b2);
+  finish(a2, c2, act[0]);
+  __syncthreads();
+  keep(act[0], h2b);
+  const f32x16_t a3 = mlp_tile<kMlpH>(act[0], lane, b2);
+  finish(a3, c3, act[1]);
+  __syncthreads();
+  keep(act[1], h3b);
+  if (wave == 0) {
+    // the fitness head: one column
+    uint4 bf[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+      bf[s] = make_uint4(0u, 0u, 0u, 0u);
+      if ((lane & 31) == 0) bf[s] = *reinterpret_cast<const uint4 *>(wf + 16 * s + 8 * (lane >> 5));
+    }
+    const f32x16_t q = mlp_tile<kMlpH>(act[1], lane, bf);
+    if ((lane & 31) == 0) {
+      const float c = cf[0];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int i = row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (i < B) t[i] = q[v] + c;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Elementwise and reduction kernels
+
+// Where the transposed bf16 copy `wt` holds parameter i: W1, W2, W3 as
+// [out][in], then Wf; -1 for the others. off: the first elements of W1, W2,
+// W3 and Wf in the flat order.
+struct MlpOffsets {
+  int64_t w1, w2, w3, wf;
+};
+__device__ __forceinline__ int64_t wt_index(const MlpOffsets &o, int64_t i) {
+  constexpr int64_t kIn = kMlpIn * kMlpH, kSq = kMlpH * kMlpH;
+  if (i < o.w1 + kIn) return i < o.w1 ? -1 : (i - o.w1) % kMlpH * kMlpIn + (i - o.w1) / kMlpH;
+  if (i < o.w2 + kSq) return i < o.w2 ? -1 : kIn + (i - o.w2) % kMlpH * kMlpH + (i - o.w2) / kMlpH;
+  if (i < o.w3 + kSq) return i < o.w3 ? -1 : kIn + kSq + (i - o.w3) % kMlpH * kMlpH + (i - o.w3) / kMlpH;
+  return i >= o.wf && i < o.wf + kMlpH ? kIn + 2 * kSq + (i - o.wf) : -1;
+}
+
+// the bf16 copies of the master weights
+__global__ void refresh_weights_kernel(const float *w, uint16_t *wb, uint16_t *wt, MlpOffsets off,
+                                       int64_t n) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const uint16_t q = f2bf(w[i]);
+    wb[i] = q;
+    const int64_t t = wt_index(off, i);
+    if (t >= 0) wt[t] = q;
+  }
+}
 
 __global__ void to_bf16_kernel(const float *x, uint16_t *y, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -224,23 +361,12 @@ __global__ void to_bf16_kernel(const float *x, uint16_t *y, int64_t n) {
     y[i] = f2bf(x[i]);
 }
 
-// raw [B][7] -> bf16 [B][16]: beta/30, ignition scaled to [-1, 1], zero pad
-__global__ void prep_input_kernel(const float *x, int B, float inv_w, float inv_h, uint16_t *xb) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * 16) return;
-  const int b = i >> 4, k = i & 15;
-  float v = 0.0f;
-  if (k < 5) v = x[b * 7 + k] * (1.0f / 30.0f);
-  else if (k == 5) v = 2.0f * x[b * 7 + 5] * inv_w - 1.0f;
-  else if (k == 6) v = 2.0f * x[b * 7 + 6] * inv_h - 1.0f;
-  xb[i] = f2bf(v);
-}
-
-// g <- g * (h > 0) (ReLU backward, in place) and its bf16 copy
-__global__ void relu_bwd_kernel(float *g, const float *h, uint16_t *gb, int64_t n) {
+// g <- g * (h > 0) (ReLU backward, in place; h the bf16 activations) and its
+// bf16 copy
+__global__ void relu_bwd_kernel(float *g, const uint16_t *h, uint16_t *gb, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const float v = h[i] > 0.0f ? g[i] : 0.0f;
+    const float v = (h[i] & 0x7FFFu) != 0 ? g[i] : 0.0f;  // (a ReLU's output is not negative)
     g[i] = v;
     gb[i] = f2bf(v);
   }
@@ -703,9 +829,9 @@ __global__ __launch_bounds__(256) void wgrad_finish_kernel(const float *part, in
 
 // ---------------------------------------------------------------------------
 // Adam (bias-corrected), fp32 master weights; wb receives the bf16 copy of
-// the updated weights the matrix products read
-__global__ void adam_kernel(float *w, uint16_t *wb, float *m, float *v, const float *g, int64_t n,
-                            float lr, float b1, float b2, float eps, float c1, float c2) {
+// the updated weights the matrix products read, wt the MLP's transposed one
+__global__ void adam_kernel(float *w, uint16_t *wb, uint16_t *wt, MlpOffsets off, float *m, float *v,
+                            const float *g, int64_t n, float lr, float b1, float b2, float eps, float c1, float c2) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const float gi = g[i];
@@ -715,7 +841,10 @@ __global__ void adam_kernel(float *w, uint16_t *wb, float *m, float *v, const fl
     v[i] = vi;
     const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
     w[i] = wi;
-    wb[i] = f2bf(wi);
+    const uint16_t q = f2bf(wi);
+    wb[i] = q;
+    const int64_t t = wt_index(off, i);
+    if (t >= 0) wt[t] = q;
   }
 }
 
@@ -910,9 +1039,10 @@ struct fire_nn {
   Layout L;
   float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // [total]
   uint16_t *wb = nullptr;                                        // bf16 copy [total]
+  uint16_t *wt = nullptr;  // bf16 W1, W2, W3 transposed ([out][in]), Wf
   // activations (max_batch rows)
   uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr, *h3b = nullptr, *d0b = nullptr, *dtb = nullptr;
-  float *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *t = nullptr, *d0 = nullptr, *d1 = nullptr,
+  float *t = nullptr, *d0 = nullptr, *d1 = nullptr,
         *d2 = nullptr, *z = nullptr;
   float *gt = nullptr, *gd0 = nullptr, *gd1 = nullptr, *gd2 = nullptr, *gz = nullptr, *gh = nullptr;
   uint16_t *ghb = nullptr;
@@ -951,30 +1081,30 @@ hipError_t nn_alloc(fire_nn *nn, T **p, int64_t count) {
 // dynamic LDS of a decoder convolution staging c planes of r x r bf16
 size_t conv_lds(int c, int r) { return sizeof(uint16_t) * (size_t)c * r * r; }
 
+MlpOffsets mlp_offsets(const Layout &L) { return {L.W1.off, L.W2.off, L.W3.off, L.Wf.off}; }
+
 hipError_t refresh_bf16(fire_nn *nn, hipStream_t s) {
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(nn->L.total)), dim3(256), 0, s, nn->w, nn->wb,
-                     nn->L.total);
+  hipLaunchKernelGGL(refresh_weights_kernel, dim3(blocks_for(nn->L.total)), dim3(256), 0, s, nn->w,
+                     nn->wb, nn->wt, mlp_offsets(nn->L), nn->L.total);
   return hipGetLastError();
 }
 
-// Forward pass; the decoder (dense layer and upsampling convolutions) runs
-// only when `want_map` (the fitness head does not depend on it).
-hipError_t forward(fire_nn *nn, const float *x, int B, hipStream_t s, bool want_map) {
+// Forward pass into t [B]; the decoder (dense layer and upsampling
+// convolutions) runs only when `want_map` (the fitness head does not depend on
+// it), and the activations are kept for it or for the backward pass (`train`).
+hipError_t forward(fire_nn *nn, const float *x, int B, hipStream_t s, bool want_map, bool train,
+                   float *t) {
   const Layout &L = nn->L;
   hipError_t e;
-  hipLaunchKernelGGL(prep_input_kernel, dim3(blocks_for((int64_t)B * 16)), dim3(256), 0, s, x, B,
-                     1.0f / (float)nn->cfg.lattice_w, 1.0f / (float)nn->cfg.lattice_h, nn->xb);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const uint16_t *wb = nn->wb;
+  const uint16_t *wb = nn->wb, *wt = nn->wt;
   const float *w = nn->w;
-  if ((e = gemm(B, kH, kIn, nn->xb, kIn, 1, wb + L.W1.off, kH, 1, nn->h1, kH, w + L.c1.off, 1, 0,
-                nn->h1b, s)) != hipSuccess) return e;
-  if ((e = gemm(B, kH, kH, nn->h1b, kH, 1, wb + L.W2.off, kH, 1, nn->h2, kH, w + L.c2.off, 1, 0,
-                nn->h2b, s)) != hipSuccess) return e;
-  if ((e = gemm(B, kH, kH, nn->h2b, kH, 1, wb + L.W3.off, kH, 1, nn->h3, kH, w + L.c3.off, 1, 0,
-                nn->h3b, s)) != hipSuccess) return e;
-  if ((e = gemm(B, 1, kH, nn->h3b, kH, 1, wb + L.Wf.off, 1, 1, nn->t, 1, w + L.cf.off, 0, 0,
-                nullptr, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(mlp_forward_kernel, dim3((B + kMlpRows - 1) / kMlpRows), dim3(kMlpThreads), 0, s,
+                     x, B, 1.0f / (float)nn->cfg.lattice_w, 1.0f / (float)nn->cfg.lattice_h, wt,
+                     wt + kIn * kH, wt + kIn * kH + kH * kH, wt + kIn * kH + 2 * kH * kH,
+                     w + L.c1.off, w + L.c2.off, w + L.c3.off, w + L.cf.off,
+                     train ? nn->xb : nullptr, train ? nn->h1b : nullptr,
+                     train ? nn->h2b : nullptr, train || want_map ? nn->h3b : nullptr, t);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!want_map) return hipSuccess;
   if ((e = gemm(B, kDec, kH, nn->h3b, kH, 1, wb + L.Wd.off, kDec, 1, nn->d0, kDec, w + L.cd.off,
                 1, 0, nn->d0b, s)) != hipSuccess) return e;
@@ -1062,10 +1192,10 @@ hipError_t backward(fire_nn *nn, const float *y_t, const uint8_t *y_map, int B, 
     if ((e = gemm(B, kH, kDec, nn->d0b, kDec, 1, wb + L.Wd.off, 1, kDec, nn->gh, kH, nullptr, 0, 1,
                   nullptr, s)) != hipSuccess) return e;
   // through the three hidden layers
-  struct Lay { const uint16_t *in_b; const float *act; const Seg *W; const Seg *c; int kin; };
-  const Lay lays[3] = {{nn->h2b, nn->h3, &L.W3, &L.c3, kH},
-                       {nn->h1b, nn->h2, &L.W2, &L.c2, kH},
-                       {nn->xb, nn->h1, &L.W1, &L.c1, kIn}};
+  struct Lay { const uint16_t *in_b, *act; const Seg *W; const Seg *c; int kin; };
+  const Lay lays[3] = {{nn->h2b, nn->h3b, &L.W3, &L.c3, kH},
+                       {nn->h1b, nn->h2b, &L.W2, &L.c2, kH},
+                       {nn->xb, nn->h1b, &L.W1, &L.c1, kIn}};
   for (int li = 0; li < 3; ++li) {
     const Lay &ly = lays[li];
     hipLaunchKernelGGL(relu_bwd_kernel, dim3(blocks_for((int64_t)B * kH)), dim3(256), 0, s, nn->gh,
@@ -1106,6 +1236,7 @@ fire_status fire_nn_create(int device, const fire_nn_cfg *cfg, uint64_t seed, fi
   if (e == hipSuccess) e = nn_alloc(nn, &nn->v, T);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->g, T);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->wb, T);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->wt, kIn * kH + 2 * kH * kH + kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->xb, Bm * kIn);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->h1b, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->h2b, Bm * kH);
@@ -1113,9 +1244,6 @@ fire_status fire_nn_create(int device, const fire_nn_cfg *cfg, uint64_t seed, fi
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d0b, Bm * kDec);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->dtb, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->ghb, Bm * kH);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->h1, Bm * kH);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->h2, Bm * kH);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->h3, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->t, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d0, Bm * kDec);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d1, Bm * kD0C * 32 * 32);
@@ -1208,8 +1336,7 @@ fire_status fire_nn_forward(fire_nn *nn, const float *x, int32_t B, float *out_t
     return nn_fail(nn, FIRE_E_INVALID, "bad batch (1..%d) or null pointer", nn->cfg.max_batch);
   NN_HIP(nn, hipSetDevice(nn->device));
   hipStream_t s = (hipStream_t)stream;
-  NN_HIP(nn, forward(nn, x, B, s, out_map != nullptr));
-  NN_HIP(nn, hipMemcpyAsync(out_t, nn->t, sizeof(float) * B, hipMemcpyDeviceToDevice, s));
+  NN_HIP(nn, forward(nn, x, B, s, out_map != nullptr, false, out_t));
   if (out_map) {
     hipLaunchKernelGGL(sigmoid_kernel, dim3(blocks_for((int64_t)B * kP)), dim3(256), 0, s, nn->z,
                        out_map, (int64_t)B * kP);
@@ -1225,7 +1352,7 @@ fire_status fire_nn_gradients(fire_nn *nn, const float *x, const float *y_t, con
     return nn_fail(nn, FIRE_E_INVALID, "bad batch (1..%d) or null pointer", nn->cfg.max_batch);
   NN_HIP(nn, hipSetDevice(nn->device));
   hipStream_t s = (hipStream_t)stream;
-  NN_HIP(nn, forward(nn, x, B, s, y_map != nullptr && nn->cfg.w_map > 0.0f));
+  NN_HIP(nn, forward(nn, x, B, s, y_map != nullptr && nn->cfg.w_map > 0.0f, true, nn->t));
   NN_HIP(nn, backward(nn, y_t, y_map, B, s));
   NN_HIP(nn, hipMemcpyAsync(out_loss, nn->loss, 2 * sizeof(float), hipMemcpyDeviceToDevice, s));
   if (out_grads)
@@ -1241,12 +1368,12 @@ fire_status fire_nn_train_step(fire_nn *nn, const float *x, const float *y_t, co
     return nn_fail(nn, FIRE_E_INVALID, "bad batch, step or learning rate");
   NN_HIP(nn, hipSetDevice(nn->device));
   hipStream_t s = (hipStream_t)stream;
-  NN_HIP(nn, forward(nn, x, B, s, y_map != nullptr && nn->cfg.w_map > 0.0f));
+  NN_HIP(nn, forward(nn, x, B, s, y_map != nullptr && nn->cfg.w_map > 0.0f, true, nn->t));
   NN_HIP(nn, backward(nn, y_t, y_map, B, s));
   const float c1 = 1.0f - powf(nn->cfg.adam_b1, (float)step);
   const float c2 = 1.0f - powf(nn->cfg.adam_b2, (float)step);
   hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(nn->L.total)), dim3(256), 0, s, nn->w, nn->wb,
-                     nn->m, nn->v, nn->g, nn->L.total, lr, nn->cfg.adam_b1, nn->cfg.adam_b2,
+                     nn->wt, mlp_offsets(nn->L), nn->m, nn->v, nn->g, nn->L.total, lr, nn->cfg.adam_b1, nn->cfg.adam_b2,
                      nn->cfg.adam_eps, c1, c2);
   NN_HIP(nn, hipGetLastError());
   if (out_loss)

@@ -168,9 +168,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const ui
     if (m < M && n < N) {
       float val = acc[v];
       if (bias) val += bias[n];
-      if (accumulate) val += C[(int64_t)m * ldc + n];
+      if (accumulate) val += C[(int64_t)m * ldc + n];  // (C is given)
       if (relu) val = fmaxf(val, 0.0f);
-      C[(int64_t)m * ldc + n] = val;
+      if (C) C[(int64_t)m * ldc + n] = val;
       if (Cb) Cb[(int64_t)m * ldc + n] = f2bf(val);
     }
   }
@@ -355,12 +355,6 @@ __global__ void refresh_weights_kernel(const float *w, uint16_t *wb, uint16_t *w
   }
 }
 
-__global__ void to_bf16_kernel(const float *x, uint16_t *y, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    y[i] = f2bf(x[i]);
-}
-
 // g <- g * (h > 0) (ReLU backward, in place; h the bf16 activations) and its
 // bf16 copy
 __global__ void relu_bwd_kernel(float *g, const uint16_t *h, uint16_t *gb, int64_t n) {
@@ -429,24 +423,6 @@ __global__ __launch_bounds__(256) void loss_fit_kernel(const float *t, const flo
   if (threadIdx.x == 0) loss[0] = s / (float)B;
 }
 
-// map head: BCE with logits, dz = w (sigmoid(z) - y) / (B P); per-block
-// partial losses reduced afterwards in fixed order
-__global__ __launch_bounds__(256) void loss_map_kernel(const float *z, const uint8_t *y,
-                                                       int64_t n, float w, float *dz,
-                                                       float *partial) {
-  __shared__ float red[256];
-  float acc = 0.0f;
-  const float inv_n = 1.0f / (float)n;
-  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const float zi = z[i], yi = y[i] ? 1.0f : 0.0f;
-    acc += fmaxf(zi, 0.0f) - zi * yi + log1pf(expf(-fabsf(zi)));
-    const float sg = 1.0f / (1.0f + expf(-zi));
-    dz[i] = w * (sg - yi) * inv_n;
-  }
-  const float s = block_reduce(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = s;
-}
-
 __global__ __launch_bounds__(256) void sum_partials_kernel(const float *p, int n, float scale,
                                                            float *out) {
   __shared__ float red[256];
@@ -456,229 +432,380 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *p, int n
   if (threadIdx.x == 0) out[0] = s * scale;
 }
 
-__global__ void sigmoid_kernel(const float *z, float *p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 1.0f / (1.0f + expf(-z[i]));
-}
-
 // ---------------------------------------------------------------------------
-// Decoder convolutions on MFMA (v_mfma_f32_16x16x32_bf16: A 16x32 with lane
-// l holding row l%16 and k 8*(l/16)..+8; B 32x16 with lane l holding column
-// l%16 and the same k; D 16x16 with lane l holding column l%16 and rows
-// 4*(l/16)..+4). A layer is out = conv3x3(up2(in)) with zero padding, in
-// [Ci=8][S][S] and out [Co][2S][2S]; the products take bf16 operands
-// (activations, kernels, back-propagated errors) and accumulate in fp32.
-// One workgroup of 4 waves per sample stages that sample's planes in LDS.
+// Decoder convolutions. A layer is out = conv3x3(up2(in)) with zero padding, in
+// [8][S][S] and out [Co][2S][2S]; activations, kernels and back-propagated
+// errors are bf16, sums fp32. Between the layers, activations and errors are
+// bf16 only (the ReLU masks come from them) and channel-interleaved,
+// [row][col][8]: a cell is one 16-byte load, store and MFMA fragment. (The dense
+// layer's d0 and its gradient are planar, [8][16][16].) Workgroups take bands
+// of rows, staged in LDS with a border of zeros so that no tap is tested
+// against the edge, and every LDS offset of a lane is fixed before the loop.
+//
+// Products on v_mfma_f32_16x16x32_bf16: A 16x32 with lane l holding row l%16
+// and k 8*(l/16)..+8; B 32x16 with lane l holding column l%16 and the same k;
+// D 16x16 with lane l holding column l%16 and rows 4*(l/16)..+4. Rows are the
+// channels and columns 16 pixels, so that a lane holds four channels of one
+// pixel and stores 8 bytes; k = tap * 8 + channel in ascending order.
+//
+// With fp32 copies of every plane, bounds tests per tap and two-byte staging,
+// a training batch of 512 spent 740 of its 890 us in these layers and the map
+// loss: last forward layer 146, its loss and bf16 copy 57, its gradients 94,
+// the other gradients 226, the other forward layers 78 us (rocprofv3). Now the
+// last layer takes 53 with the loss (its exponentials and 32 products a pixel on
+// VALU), its gradients 42 (73 sums a thread on VALU; 84 MB of traffic would
+// take 18 at the 4.8 TB/s of a copy), the others 20 + 20 + 10 + 7 and 18 + 8 us,
+// and the batch 442 us.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 constexpr int kConvCi = 8, kConvTaps = 9, kConvK = kConvCi * kConvTaps;  // 72
 constexpr int kWgradCols = 80;  // 72 kernel taps, the bias column, padding
 constexpr int kWgradRows = 16;  // output channels, padded
 constexpr int kWgradParts = 2048;
+// workgroups of the gradient kernels that keep sums across samples: each adds
+// its sums once, so a few samples a workgroup pay for it
+constexpr int kConvGrid = 512, kCo1Grid = 1024;
 
-__device__ __forceinline__ bf16x8_t as_bf16x8(u16x8_t v) { return __builtin_bit_cast(bf16x8_t, v); }
-
-// Stage n bf16 values (n a multiple of 8, 16-byte aligned) into LDS.
-__device__ __forceinline__ void stage_bf16(uint16_t *dst, const uint16_t *src, int n) {
-  for (int i = threadIdx.x; i < n / 8; i += blockDim.x)
-    reinterpret_cast<uint4 *>(dst)[i] = reinterpret_cast<const uint4 *>(src)[i];
+__device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
+__device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+__device__ __forceinline__ float bf16_lo(uint32_t d) { return __uint_as_float(d << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t d) { return __uint_as_float(d & 0xFFFF0000u); }
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
 }
 
-// Forward (UP) or data gradient (!UP) of one layer, 16-pixel tiles of the
-// 2S x 2S grid:
-//   UP:  out[co][y][x] = bias[co] + sum_k A[p][k] B[k][co],
-//        A[p][k] = in[ci][(y+dy-1)/2][(x+dx-1)/2], B[k][co] = K[co][ci][dy][dx];
-//        written fp32 (and bf16) after an optional ReLU;
-//  !UP:  dU[ci][u][v] = sum_k A[p][k] B[k][ci],
-//        A[p][k] = g[co][u-dy+1][v-dx+1], B[k][ci] = K[co][ci][dy][dx];
-//        the 2x2 blocks of dU are summed into din[ci][u/2][v/2], which is
-//        zeroed where act <= 0.
-// src: UP the layer input [8][S][S], !UP the error g [8][2S][2S] (bf16;
-// the one-channel data gradient of the last layer runs in
-// upconv_grads_co1_kernel). The 8 source planes are staged
-// channel-interleaved, [row][col][channel], and k = tap * 8 + channel: a
-// lane's 8 k-values of a step are the 8 channels of one source cell, one
-// 16-byte LDS read.
-template <bool UP>
-__global__ __launch_bounds__(256) void upconv_mfma_kernel(const uint16_t *src, const uint16_t *Kb,
-                                                          const float *bias, int S, int Co,
-                                                          int relu, const float *act, float *out,
-                                                          uint16_t *out_b) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t plane[];
-  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int O = 2 * S;
-  const int srcR = UP ? S : O;
-  const uint16_t *sp = src + (int64_t)b * kConvCi * srcR * srcR;
-  {
-    const int n = srcR * srcR;
-    for (int i = threadIdx.x; i < kConvCi * n; i += blockDim.x)
-      plane[(i % n) * kConvCi + i / n] = sp[i];
+// Cell (y, x) of a sample's [8][R][R] planes (PLANAR) or [R][R][8] cells.
+template <bool PLANAR>
+__device__ __forceinline__ uint4 load_cell(const uint16_t *src, int R, int y, int x) {
+  if constexpr (PLANAR) {
+    uint16_t v[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = src[(c * R + y) * R + x];
+    return make_uint4((uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16),
+                      (uint32_t)v[4] | ((uint32_t)v[5] << 16), (uint32_t)v[6] | ((uint32_t)v[7] << 16));
+  } else {
+    return reinterpret_cast<const uint4 *>(src)[y * R + x];
   }
-  const int col = lane & 15, kq = lane >> 4;
-  const int ncols = UP ? Co : kConvCi;  // columns of the result
-  const int nk = kConvTaps * kConvCi;
-  const int steps = (nk + 31) / 32;
-  // B fragments of the (up to) three k-steps
-  bf16x8_t bw[3];
+}
+
+// Rows row0 - 1 .. row0 + rows of a sample's R x R cells with a column to each
+// side, zero outside, into cells [rows + 2][R + 2].
+template <bool PLANAR>
+__device__ __forceinline__ void stage_cells(uint4 *cells, const uint16_t *src, int R, int row0, int rows) {
+  for (int i = threadIdx.x; i < (rows + 2) * (R + 2); i += blockDim.x) {
+    const int y = row0 - 1 + i / (R + 2), x = i % (R + 2) - 1;
+    cells[i] = (unsigned)y < (unsigned)R && (unsigned)x < (unsigned)R ? load_cell<PLANAR>(src, R, y, x)
+                                                                      : make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+
+// Kernel fragments of the three k-steps for row `row` of the result: FWD the
+// output channel (k over tap, input channel), else the input channel.
+template <bool FWD>
+__device__ __forceinline__ void kernel_fragments(const uint16_t *Kb, int row, int kq, bf16x8_t (&w)[3]) {
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
+    const int t = 4 * s + kq;
     u16x8_t v;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int k = 32 * s + 8 * kq + i;
-      const int t = k / kConvCi, c = k % kConvCi;
-      // UP: column col is co, k runs over (tap, ci). !UP: column col is ci,
-      // k runs over (tap, co)
-      const bool ok = k < nk && col < ncols;
-      const int widx = UP ? (col * kConvCi + c) * kConvTaps + t : (c * kConvCi + col) * kConvTaps + t;
-      v[i] = ok ? Kb[widx] : (uint16_t)0;
-    }
-    bw[s] = as_bf16x8(v);
-  }
-  const float bcol = (UP && col < ncols && bias) ? bias[col] : 0.0f;
-  __syncthreads();
-  // tile: 16 consecutive columns x0.. of one row; for !UP a wave takes the
-  // two rows of a 2x2 block together
-  const int per_row = O / 16;
-  const int rows_per_item = UP ? 1 : 2;
-  const int items = (O / rows_per_item) * per_row;
-  const int sgn = UP ? 1 : -1;
-  for (int it = wave; it < items; it += 4) {
-    const int y0 = (it / per_row) * rows_per_item, x0 = (it % per_row) * 16;
-    const int x = x0 + (lane & 15);
-    f32x4_t acc[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) acc[r] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      if (r >= rows_per_item) break;
-      const int y = y0 + r;
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        if (s >= steps) break;
-        u16x8_t a;
-        // tap 4 s + kq, the 8 channels of one source cell
-        const int t = 4 * s + kq;
-        const int yy = y + sgn * (t / 3 - 1), xx = x + sgn * (t % 3 - 1);
-        const bool in = t < kConvTaps && (unsigned)yy < (unsigned)O && (unsigned)xx < (unsigned)O;
-        const int sy = UP ? (yy >> 1) : yy, sx = UP ? (xx >> 1) : xx;
-        if (in) {
-          a = *reinterpret_cast<const u16x8_t *>(&plane[(sy * srcR + sx) * kConvCi]);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) a[i] = 0;
-        }
-        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), bw[s], acc[r], 0, 0, 0);
-      }
-    }
-    if (col >= ncols) continue;
-    if (UP) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float val = acc[0][v] + bcol;
-        if (relu) val = fmaxf(val, 0.0f);
-        const int64_t o = (((int64_t)b * Co + col) * O + y0) * O + x0 + 4 * kq + v;
-        out[o] = val;
-        if (out_b) out_b[o] = f2bf(val);
-      }
-    } else {
-      // lane holds dU[col][y0 + r][x0 + 4kq + v]: pairs of columns in the
-      // lane, the two rows in acc[0] and acc[1]
-      const int sy = y0 >> 1;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const float sum = (acc[0][2 * h] + acc[0][2 * h + 1]) + (acc[1][2 * h] + acc[1][2 * h + 1]);
-        const int sx = (x0 >> 1) + 2 * kq + h;
-        const int64_t o = (((int64_t)b * kConvCi + col) * S + sy) * S + sx;
-        const float val = act[o] > 0.0f ? sum : 0.0f;
-        out[o] = val;
-        if (out_b) out_b[o] = f2bf(val);
-      }
-    }
+    for (int i = 0; i < 8; ++i)
+      v[i] = t < kConvTaps && row < kConvCi
+                 ? Kb[FWD ? (row * kConvCi + i) * kConvTaps + t : (i * kConvCi + row) * kConvTaps + t]
+                 : (uint16_t)0;
+    w[s] = __builtin_bit_cast(bf16x8_t, v);
   }
 }
 
-// Kernel and bias gradients of one layer: for every sample handled by this
-// workgroup (b = blockIdx.x, + gridDim.x, ...) the contraction over its
-// (2S)^2 pixels, 32 per MFMA step:
+// Forward, 8 output channels: out[y][x][co] = relu(bias[co] + sum over taps and
+// channels of K[co][ci][dy][dx] in[(y+dy-1)/2][(x+dx-1)/2][ci]). A
+// workgroup: kBand output rows of a sample; a wave's rows have one parity, so the
+// source cells of its taps lie at fixed offsets from the pixel's cell.
+template <int S, bool PLANAR_IN>
+__global__ __launch_bounds__(256) void upconv_kernel(const uint16_t *src, const uint16_t *Kb,
+                                                     const float *bias, uint16_t *out) {
+  constexpr int O = 2 * S, kBand = 32, kBands = O / kBand, kLd = S + 2;
+  __shared__ __attribute__((aligned(16))) uint4 cells[(kBand / 2 + 2) * kLd];
+  const int b = blockIdx.x / kBands, y0 = (blockIdx.x % kBands) * kBand;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, px = lane & 15, kq = lane >> 4;
+  stage_cells<PLANAR_IN>(cells, src + (int64_t)b * kConvCi * S * S, S, y0 / 2, kBand / 2);
+  bf16x8_t w[3];
+  kernel_fragments<true>(Kb, px, kq, w);
+  float bc[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) bc[v] = kq < 2 ? bias[4 * kq + v] : 0.0f;
+  int off[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int t = min(4 * s + kq, kConvTaps - 1);
+    off[s] = ((((wave & 1) + t / 3 - 1) >> 1) + 1) * kLd + (((px & 1) + t % 3 - 1) >> 1) + 1 + (px >> 1);
+  }
+  __syncthreads();
+  for (int r = wave; r < kBand; r += 4)
+#pragma unroll
+    for (int x0 = 0; x0 < O; x0 += 16) {
+      const int base = (r >> 1) * kLd + x0 / 2;
+      f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        // (the third step has one tap: the other lanes read a border cell, zero)
+        const int at = s < 2 || kq == 0 ? base + off[s] : 0;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], as_bf16x8(cells[at]), acc, 0, 0, 0);
+      }
+      if (kq < 2) {
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[i] + bc[i], 0.0f);
+        *reinterpret_cast<uint2 *>(out + (((int64_t)b * O + y0 + r) * O + x0 + px) * kConvCi + 4 * kq) =
+            make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+      }
+    }
+}
+
+// Last layer, one output channel, S = 64: an MFMA would fill one row of 16, so
+// a thread takes an input cell and computes its four output pixels on VALU.
+// With nearest upsampling the nine taps of a pixel read four cells, and the
+// taps on one cell are added first (fp32): 32 products a pixel. The epilogue
+// is fused: TRAIN the map loss and its gradient, dz = w (sigmoid(z) - y) / n in
+// bf16, the workgroup's partial loss to partial[block]; else sigmoid(z).
+constexpr int kLastS = 64, kLastBand = 16, kLastBands = kLastS / kLastBand;  // cell rows a workgroup
+template <bool TRAIN>
+__global__ __launch_bounds__(256) void last_layer_kernel(const uint16_t *src, const uint16_t *Kb,
+                                                         const float *bias, const uint8_t *y_map,
+                                                         float w_map, float inv_n, uint16_t *gz,
+                                                         float *partial, float *map) {
+  constexpr int S = kLastS, O = 2 * S, kLd = S + 2;
+  __shared__ __attribute__((aligned(16))) uint4 cells[(kLastBand + 2) * kLd];
+  __shared__ __attribute__((aligned(16))) float4 wk[4][kConvCi];  // [parity][channel], its four cells
+  __shared__ float red[256];
+  const int b = blockIdx.x / kLastBands, Y0 = (blockIdx.x % kLastBands) * kLastBand, t = threadIdx.x;
+  stage_cells<false>(cells, src + (int64_t)b * kConvCi * S * S, S, Y0, kLastBand);
+  if (t < 4 * kConvCi * 4) {
+    // cell (i, j) of parity (py, px): rows py - 1 + i, taps dy that read it
+    const int j = t & 1, i = (t >> 1) & 1, c = (t >> 2) & 7, px = (t >> 5) & 1, py = t >> 6;
+    float sum = 0.0f;
+    for (int dy = 0; dy < 3; ++dy)
+      for (int dx = 0; dx < 3; ++dx)
+        if (((py + dy - 1) >> 1) == py - 1 + i && ((px + dx - 1) >> 1) == px - 1 + j)
+          sum += bf16_f32(Kb[c * kConvTaps + 3 * dy + dx]);
+    reinterpret_cast<float *>(&wk[2 * py + px][c])[2 * i + j] = sum;
+  }
+  const float bc = bias[0];
+  __syncthreads();
+  float acc_loss = 0.0f;
+  for (int q = t; q < kLastBand * S; q += 256) {
+    const int r = q / S, X = q % S;
+    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    const uint32_t *cw = reinterpret_cast<const uint32_t *>(&cells[r * kLd + X]);
+    // two channels at a time (all eight unrolled, the compiler keeps the 128
+    // weights in registers and two waves a SIMD)
+#pragma unroll 1
+    for (int c = 0; c < kConvCi; c += 2) {
+      uint32_t d[9];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) d[k] = cw[((k / 3) * kLd + k % 3) * 4 + c / 2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float v[9];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) v[k] = h ? bf16_hi(d[k]) : bf16_lo(d[k]);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const float4 k4 = wk[p][c + h];
+          const int o = 3 * (p >> 1) + (p & 1);
+          z[p] = fmaf(k4.x, v[o], z[p]);
+          z[p] = fmaf(k4.y, v[o + 1], z[p]);
+          z[p] = fmaf(k4.z, v[o + 3], z[p]);
+          z[p] = fmaf(k4.w, v[o + 4], z[p]);
+        }
+      }
+    }
+#pragma unroll
+    for (int py = 0; py < 2; ++py) {
+      const int64_t o = ((int64_t)b * O + 2 * (Y0 + r) + py) * O + 2 * X;
+      if constexpr (TRAIN) {
+        float dz[2];
+#pragma unroll
+        for (int px = 0; px < 2; ++px) {
+          const float zi = z[2 * py + px] + bc, yi = y_map[o + px] ? 1.0f : 0.0f;
+          acc_loss += fmaxf(zi, 0.0f) - zi * yi + log1pf(expf(-fabsf(zi)));
+          const float sg = 1.0f / (1.0f + expf(-zi));
+          dz[px] = w_map * (sg - yi) * inv_n;
+        }
+        *reinterpret_cast<uint32_t *>(gz + o) = pack_bf16(dz[0], dz[1]);
+      } else {
+        map[o] = 1.0f / (1.0f + expf(-(z[2 * py] + bc)));
+        map[o + 1] = 1.0f / (1.0f + expf(-(z[2 * py + 1] + bc)));
+      }
+    }
+  }
+  if constexpr (TRAIN) {
+    const float sum = block_reduce(acc_loss, red);
+    if (t == 0) partial[blockIdx.x] = sum;
+  }
+}
+
+// Data gradient of a layer with 8 output channels: dU[u][v][ci] = sum over taps
+// and channels of K[co][ci][dy][dx] g[u-dy+1][v-dx+1][co]; the 2x2 blocks of dU
+// are summed (columns across two lanes, rows in the lane) and zeroed where the
+// layer's input act is 0 (it is a ReLU's output). PLANAR: act and out are the
+// dense layer's planes (out may be act: an element is read by the lane that
+// then writes it) and the fp32 gradient goes to out_f too. A workgroup:
+// kBand rows of a sample's 2S x 2S grid.
+template <int S, bool PLANAR>
+__global__ __launch_bounds__(256) void upconv_dgrad_kernel(const uint16_t *g, const uint16_t *Kb,
+                                                           const uint16_t *act, uint16_t *out, float *out_f) {
+  constexpr int O = 2 * S, kBand = 16, kBands = O / kBand, kLd = O + 2;
+  __shared__ __attribute__((aligned(16))) uint4 cells[(kBand + 2) * kLd];
+  const int b = blockIdx.x / kBands, u0 = (blockIdx.x % kBands) * kBand;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, px = lane & 15, kq = lane >> 4;
+  stage_cells<false>(cells, g + (int64_t)b * kConvCi * O * O, O, u0, kBand);
+  bf16x8_t w[3];
+  kernel_fragments<false>(Kb, px, kq, w);
+  int off[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int t = min(4 * s + kq, kConvTaps - 1);
+    off[s] = (2 - t / 3) * kLd + 2 - t % 3 + px;
+  }
+  __syncthreads();
+  for (int r = 2 * wave; r < kBand; r += 8)
+#pragma unroll
+    for (int x0 = 0; x0 < O; x0 += 16) {
+      f32x4_t acc[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        acc[h] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        const int base = (r + h) * kLd + x0;
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const int at = s < 2 || kq == 0 ? base + off[s] : 0;
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s], as_bf16x8(cells[at]), acc[h], 0, 0, 0);
+        }
+      }
+      float sum[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float a[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)  // plus the neighbouring column's (lanes 1 0 3 2 of a quad)
+          a[h] = acc[h][v] + __int_as_float(__builtin_amdgcn_update_dpp(
+                                 0, __float_as_int(acc[h][v]), 0xB1, 0xF, 0xF, true));
+        sum[v] = a[0] + a[1];
+      }
+      if (kq < 2 && (px & 1) == 0) {
+        const int sy = (u0 + r) >> 1, sx = (x0 + px) >> 1;
+        if constexpr (PLANAR) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int64_t o = (((int64_t)b * kConvCi + 4 * kq + v) * S + sy) * S + sx;
+            const float val = (act[o] & 0x7FFFu) ? sum[v] : 0.0f;
+            out_f[o] = val;
+            out[o] = f2bf(val);
+          }
+        } else {
+          const int64_t o = (((int64_t)b * S + sy) * S + sx) * kConvCi + 4 * kq;
+          const uint2 m = *reinterpret_cast<const uint2 *>(act + o);
+          *reinterpret_cast<uint2 *>(out + o) =
+              make_uint2(pack_bf16((m.x & 0x7FFFu) ? sum[0] : 0.0f, (m.x & 0x7FFF0000u) ? sum[1] : 0.0f),
+                         pack_bf16((m.y & 0x7FFFu) ? sum[2] : 0.0f, (m.y & 0x7FFF0000u) ? sum[3] : 0.0f));
+        }
+      }
+    }
+}
+
+// Kernel and bias gradients of a layer with 8 output channels: the contraction
+// over the (2S)^2 pixels of every (sample, band) this workgroup takes, 32 per
+// MFMA step:
 //   P[co][k] += sum_p A[co][p] B[p][k],  A[co][p] = g[co][p] (bf16 error),
 //   B[p][k] = in[ci][(y+dy-1)/2][(x+dx-1)/2] for k = ci*9 + dy*3 + dx < 72,
-//   1 for k = 72 (the bias gradient), 0 beyond;
+//   1 for k = 72 (the bias gradient; columns beyond it are not used);
 // the four waves' sums are added in wave order and the workgroup writes its
-// partial [16][80] to part; wgrad_finish_kernel adds the partials.
-__global__ __launch_bounds__(256) void upconv_wgrad_mfma_kernel(const uint16_t *g_b,
-                                                                const uint16_t *in_b, int B, int S,
-                                                                int Co, float *part) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds16[];
-  __shared__ float red[4][kWgradRows * kWgradCols];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int O = 2 * S;
-  uint16_t *gpl = lds16;                        // [Co][O][O]
-  uint16_t *ipl = lds16 + (Co * O * O + 7) / 8 * 8;  // [8][S][S]
+// partial [16][80] to part; wgrad_finish_kernel adds the partials. Both
+// operands run along pixels, so they are staged planar: the errors with a
+// 16-byte skew per plane, the inputs with zero borders and a plane of ones.
+// A lane's eight pixels of B read five cells of a row, each twice but for the
+// ends: three LDS reads and four byte permutations, whose selectors depend on
+// the lane's dx only.
+template <int S, bool PLANAR_IN>
+__global__ __launch_bounds__(256) void upconv_wgrad_kernel(const uint16_t *g_b, const uint16_t *in_b, int B,
+                                                           float *part) {
+  constexpr int O = 2 * S, kBand = 32, kBands = O / kBand, kRows = kBand / 2 + 2;
+  constexpr int kGLd = kBand * O + 8, kRs = S + 8, kPl = kRows * kRs;
+  // the waves' sums take the planes' place at the end
+  __shared__ __attribute__((aligned(16))) uint16_t planes[kConvCi * kGLd + (kConvCi + 1) * kPl];
+  static_assert(sizeof(planes) >= sizeof(float) * 4 * kWgradRows * kWgradCols, "");
+  uint16_t *const gpl = planes, *const ipl = planes + kConvCi * kGLd;
+  float(*const red)[kWgradRows * kWgradCols] =
+      reinterpret_cast<float(*)[kWgradRows * kWgradCols]>(planes);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = lane & 15, kq = lane >> 4;
   // each lane's B column per n-tile: k = 16 n + row
-  int bc[5], bdy[5], bdx[5];
+  int pl[5], dyv[5];
+  uint32_t sa[5], sb[5];
 #pragma unroll
   for (int n = 0; n < 5; ++n) {
-    const int k = 16 * n + row;
-    bc[n] = k < kConvK ? k / kConvTaps : (k == kConvK ? -2 : -1);
-    bdy[n] = (k % kConvTaps) / 3;
-    bdx[n] = (k % kConvTaps) % 3;
+    const int k = 16 * n + row, dx = (k % kConvTaps) % 3;
+    pl[n] = (k < kConvK ? k / kConvTaps : kConvCi) * kPl + 4;
+    dyv[n] = k < kConvK ? (k % kConvTaps) / 3 : 1;
+    sa[n] = dx == 0 ? 0x05040302u : dx == 1 ? 0x05040504u : 0x07060504u;
+    sb[n] = dx == 0 ? 0x03020100u : dx == 1 ? 0x03020302u : 0x05040302u;
   }
   f32x4_t acc[5];
 #pragma unroll
   for (int n = 0; n < 5; ++n) acc[n] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-  const int chunks = O * O / 32;
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
+  // borders and the plane of ones: written once, the staging leaves them
+  for (int i = tid; i < (kConvCi + 1) * kPl; i += 256) ipl[i] = i < kConvCi * kPl ? 0u : 0x3F80u;
+  for (int item = blockIdx.x; item < B * kBands; item += gridDim.x) {
+    const int b = item / kBands, y0 = (item % kBands) * kBand;
     __syncthreads();
-    stage_bf16(gpl, g_b + (int64_t)b * Co * O * O, Co * O * O);
-    stage_bf16(ipl, in_b + (int64_t)b * kConvCi * S * S, kConvCi * S * S);
-    __syncthreads();
-    for (int ch = wave; ch < chunks; ch += 4) {
-      const int p0 = ch * 32 + 8 * kq;  // this lane's 8 pixels (one row)
-      const int y = p0 / O, x0 = p0 % O;
-      u16x8_t a;
-      if (row < Co) {
-        a = *reinterpret_cast<const u16x8_t *>(&gpl[(row * O + y) * O + x0]);
-      } else {
+    const uint4 *g = reinterpret_cast<const uint4 *>(g_b + ((int64_t)b * O + y0) * O * kConvCi);
+    for (int i = tid; i < kBand * O / 2; i += 256) {
+      const uint4 p = g[2 * i], q = g[2 * i + 1];
+      const uint32_t pw[4] = {p.x, p.y, p.z, p.w}, qw[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a[i] = 0;
-      }
-      const bf16x8_t av = as_bf16x8(a);
+      for (int c = 0; c < kConvCi; ++c)
+        *reinterpret_cast<uint32_t *>(&gpl[c * kGLd + 2 * i]) =
+            __builtin_amdgcn_perm(qw[c / 2], pw[c / 2], c & 1 ? 0x07060302u : 0x05040100u);
+    }
+    const uint16_t *in = in_b + (int64_t)b * kConvCi * S * S;
+    for (int i = tid; i < kRows * S; i += 256) {
+      const int r = i / S, x = i % S, y = y0 / 2 - 1 + r;
+      const uint4 p = (unsigned)y < (unsigned)S ? load_cell<PLANAR_IN>(in, S, y, x) : make_uint4(0u, 0u, 0u, 0u);
+      const uint32_t pw[4] = {p.x, p.y, p.z, p.w};
+#pragma unroll
+      for (int c = 0; c < kConvCi; ++c)
+        ipl[c * kPl + r * kRs + 4 + x] = (uint16_t)(c & 1 ? pw[c / 2] >> 16 : pw[c / 2]);
+    }
+    __syncthreads();
+    for (int ch = wave; ch < kBand * O / 32; ch += 4) {
+      const int p0 = ch * 32 + 8 * kq;  // this lane's 8 pixels (one row)
+      const int y = p0 / O, c0 = (p0 % O) / 2;
+      const uint4 a = row < kConvCi ? *reinterpret_cast<const uint4 *>(&gpl[row * kGLd + p0])
+                                    : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
       for (int n = 0; n < 5; ++n) {
-        u16x8_t bv;
-        const int c = bc[n];
-        const int yy = y + bdy[n] - 1;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int xx = x0 + i + bdx[n] - 1;
-          uint16_t v = 0;
-          if (c >= 0) {
-            if ((unsigned)yy < (unsigned)O && (unsigned)xx < (unsigned)O)
-              v = ipl[(c * S + (yy >> 1)) * S + (xx >> 1)];
-          } else if (c == -2) {
-            v = 0x3F80u;  // 1.0
-          }
-          bv[i] = v;
-        }
-        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(bv), acc[n], 0, 0, 0);
+        // cells c0 - 2 .. c0 + 5 of the row that the lane's dy reads
+        const uint16_t *q = &ipl[pl[n] + (((y + dyv[n] - 1) >> 1) + 1) * kRs + c0];
+        const uint32_t wm = *reinterpret_cast<const uint32_t *>(q - 2);
+        const uint2 wc = *reinterpret_cast<const uint2 *>(q);
+        const uint32_t wp = *reinterpret_cast<const uint32_t *>(q + 4);
+        const uint4 bv = make_uint4(__builtin_amdgcn_perm(wc.x, wm, sa[n]), __builtin_amdgcn_perm(wc.y, wc.x, sb[n]),
+                                    __builtin_amdgcn_perm(wc.y, wc.x, sa[n]), __builtin_amdgcn_perm(wp, wc.y, sb[n]));
+        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), as_bf16x8(bv), acc[n], 0, 0, 0);
       }
     }
   }
+  __syncthreads();
   // D layout: lane holds column (16 n + row) and rows (co) 4 kq + v
 #pragma unroll
   for (int n = 0; n < 5; ++n)
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][(4 * kq + v) * kWgradCols + 16 * n + row] = acc[n][v];
   __syncthreads();
-  for (int i = threadIdx.x; i < kWgradRows * kWgradCols; i += blockDim.x)
+  for (int i = tid; i < kWgradRows * kWgradCols; i += 256)
     part[(int64_t)blockIdx.x * kWgradRows * kWgradCols + i] =
         ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
 }
-
-__device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 // Kernel, bias and data gradients of a layer with one output channel (the
 // last decoder layer), on the input's own grid. With nearest 2x upsampling,
@@ -693,21 +820,19 @@ __device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((
 // {2X, 2X+1}. With one output channel an MFMA tile would use one of its 16
 // rows, so this runs on VALU. Thread item: one sample's input cells
 // (Y, 2j) and (Y, 2j + 1); their error windows, rows 2Y-1 .. 2Y+2 and
-// columns 4j-1 .. 4j+4, are three 8-byte loads per row, their inputs one
-// 4-byte load per channel. Items are spread over the grid; each thread
-// keeps 73 sums, reduced over the wave (a fixed shuffle tree) and then over
+// columns 4j-1 .. 4j+4, are three 8-byte loads per row, their inputs two
+// 16-byte loads. Items are spread over the grid; each thread keeps 73 sums, reduced over the wave (a fixed shuffle tree) and then over
 // the four waves in order, so the result does not depend on timing.
 // Partials [gridDim.x][16][80] (row 0) as the MFMA form. S even, S <= 64.
 // The same box sums also give the layer's data gradient: the
 // error of input cell (Y, X), summed over its 2x2 upsampling block, is
 // sum over taps of K[c][dy][dx] times box (dy, dx); it is zeroed where the
-// layer input's activation act <= 0 and written to din (fp32) and din_b
-// (bf16), as the MFMA data-gradient kernel writes it.
-__global__ __launch_bounds__(256) void upconv_grads_co1_kernel(const uint16_t *g_b,
-                                                               const uint16_t *in_b, int B, int S,
-                                                               float *part, const uint16_t *Kb,
-                                                               const float *act, float *din,
-                                                               uint16_t *din_b) {
+// layer's input (a ReLU's output) is 0 and written to din_b.
+__global__ __launch_bounds__(256) void upconv_grads_co1_kernel(const uint16_t *__restrict__ g_b,
+                                                               const uint16_t *__restrict__ in_b,
+                                                               int B, int S, float *__restrict__ part,
+                                                               const uint16_t *__restrict__ Kb,
+                                                               uint16_t *__restrict__ din_b) {
   __shared__ float red[4][kConvK + 1];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int O = 2 * S, half = S / 2;
@@ -716,7 +841,8 @@ __global__ __launch_bounds__(256) void upconv_grads_co1_kernel(const uint16_t *g
   for (int k = 0; k <= kConvK; ++k) acc[k] = 0.0f;
   float kw[kConvK];
 #pragma unroll
-  for (int k = 0; k < kConvK; ++k) kw[k] = bf16_f32(Kb[k]);
+  for (int k = 0; k < kConvK; ++k)  // (uniform: scalar registers)
+    kw[k] = __uint_as_float(__builtin_amdgcn_readfirstlane((uint32_t)Kb[k] << 16));
   const int64_t items = (int64_t)B * S * half;
   for (int64_t it = (int64_t)blockIdx.x * blockDim.x + t; it < items;
        it += (int64_t)gridDim.x * blockDim.x) {
@@ -742,13 +868,14 @@ __global__ __launch_bounds__(256) void upconv_grads_co1_kernel(const uint16_t *g
       w[i][4] = __uint_as_float(q1.y & 0xFFFF0000u);
       w[i][5] = __uint_as_float(q2.x << 16);
     }
+    const uint4 *ip = reinterpret_cast<const uint4 *>(in_b) + ((int64_t)b * S + Y) * S + 2 * j;
+    const uint4 p0 = ip[0], p1 = ip[1];
+    const uint32_t w0[4] = {p0.x, p0.y, p0.z, p0.w}, w1[4] = {p1.x, p1.y, p1.z, p1.w};
     float v0[kConvCi], v1[kConvCi];
 #pragma unroll
     for (int c = 0; c < kConvCi; ++c) {
-      const uint32_t pv =
-          *reinterpret_cast<const uint32_t *>(in_b + ((int64_t)(b * kConvCi + c) * S + Y) * S + 2 * j);
-      v0[c] = __uint_as_float(pv << 16);
-      v1[c] = __uint_as_float(pv & 0xFFFF0000u);
+      v0[c] = c & 1 ? bf16_hi(w0[c / 2]) : bf16_lo(w0[c / 2]);
+      v1[c] = c & 1 ? bf16_hi(w1[c / 2]) : bf16_lo(w1[c / 2]);
     }
     float dsum[2][kConvCi];
 #pragma unroll
@@ -778,12 +905,12 @@ __global__ __launch_bounds__(256) void upconv_grads_co1_kernel(const uint16_t *g
       acc[kConvK] += (w[1][2 * h + 1] + w[1][2 * h + 2]) + (w[2][2 * h + 1] + w[2][2 * h + 2]);
     }
 #pragma unroll
-    for (int c = 0; c < kConvCi; ++c) {
-      const int64_t o = ((int64_t)(b * kConvCi + c) * S + Y) * S + 2 * j;
-      const float2 a = *reinterpret_cast<const float2 *>(act + o);
-      const float r0 = a.x > 0.0f ? dsum[0][c] : 0.0f, r1 = a.y > 0.0f ? dsum[1][c] : 0.0f;
-      *reinterpret_cast<float2 *>(din + o) = make_float2(r0, r1);
-      *reinterpret_cast<uint32_t *>(din_b + o) = (uint32_t)f2bf(r0) | ((uint32_t)f2bf(r1) << 16);
+    for (int h = 0; h < 2; ++h) {
+      float d[kConvCi];
+#pragma unroll
+      for (int c = 0; c < kConvCi; ++c) d[c] = (h ? v1[c] : v0[c]) > 0.0f ? dsum[h][c] : 0.0f;
+      reinterpret_cast<uint4 *>(din_b)[((int64_t)b * S + Y) * S + 2 * j + h] = make_uint4(
+          pack_bf16(d[0], d[1]), pack_bf16(d[2], d[3]), pack_bf16(d[4], d[5]), pack_bf16(d[6], d[7]));
     }
   }
 #pragma unroll
@@ -1042,9 +1169,8 @@ struct fire_nn {
   uint16_t *wt = nullptr;  // bf16 W1, W2, W3 transposed ([out][in]), Wf
   // activations (max_batch rows)
   uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr, *h3b = nullptr, *d0b = nullptr, *dtb = nullptr;
-  float *t = nullptr, *d0 = nullptr, *d1 = nullptr,
-        *d2 = nullptr, *z = nullptr;
-  float *gt = nullptr, *gd0 = nullptr, *gd1 = nullptr, *gd2 = nullptr, *gz = nullptr, *gh = nullptr;
+  float *t = nullptr;
+  float *gt = nullptr, *gd0 = nullptr, *gh = nullptr;
   uint16_t *ghb = nullptr;
   // bf16 copies the decoder's MFMA convolutions read
   uint16_t *d1b = nullptr, *d2b = nullptr, *gzb = nullptr, *gd1b = nullptr, *gd2b = nullptr;
@@ -1078,9 +1204,6 @@ hipError_t nn_alloc(fire_nn *nn, T **p, int64_t count) {
   return e;
 }
 
-// dynamic LDS of a decoder convolution staging c planes of r x r bf16
-size_t conv_lds(int c, int r) { return sizeof(uint16_t) * (size_t)c * r * r; }
-
 MlpOffsets mlp_offsets(const Layout &L) { return {L.W1.off, L.W2.off, L.W3.off, L.Wf.off}; }
 
 hipError_t refresh_bf16(fire_nn *nn, hipStream_t s) {
@@ -1106,29 +1229,27 @@ hipError_t forward(fire_nn *nn, const float *x, int B, hipStream_t s, bool want_
                      train ? nn->h2b : nullptr, train || want_map ? nn->h3b : nullptr, t);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!want_map) return hipSuccess;
-  if ((e = gemm(B, kDec, kH, nn->h3b, kH, 1, wb + L.Wd.off, kDec, 1, nn->d0, kDec, w + L.cd.off,
+  if ((e = gemm(B, kDec, kH, nn->h3b, kH, 1, wb + L.Wd.off, kDec, 1, nullptr, kDec, w + L.cd.off,
                 1, 0, nn->d0b, s)) != hipSuccess) return e;
-  // decoder: d0b (bf16 of d0, from the dense layer) -> d1 -> d2 -> z
-  hipLaunchKernelGGL((upconv_mfma_kernel<true>), dim3(B), dim3(256), conv_lds(kD0C, 16), s,
-                     nn->d0b, wb + L.K1.off, w + L.k1.off, 16, kD0C, 1, nullptr, nn->d1, nn->d1b);
-  hipLaunchKernelGGL((upconv_mfma_kernel<true>), dim3(B), dim3(256), conv_lds(kD0C, 32), s,
-                     nn->d1b, wb + L.K2.off, w + L.k2.off, 32, kD0C, 1, nullptr, nn->d2, nn->d2b);
-  hipLaunchKernelGGL((upconv_mfma_kernel<true>), dim3(B), dim3(256), conv_lds(kD0C, 64), s,
-                     nn->d2b, wb + L.K3.off, w + L.k3.off, 64, 1, 0, nullptr, nn->z, nullptr);
+  // decoder: d0b (the dense layer's output) -> d1b -> d2b
+  hipLaunchKernelGGL((upconv_kernel<16, true>), dim3(B), dim3(256), 0, s, nn->d0b, wb + L.K1.off,
+                     w + L.k1.off, nn->d1b);
+  hipLaunchKernelGGL((upconv_kernel<32, false>), dim3(2 * B), dim3(256), 0, s, nn->d1b, wb + L.K2.off,
+                     w + L.k2.off, nn->d2b);
   return hipGetLastError();
 }
 
-// Kernel and bias gradients of one decoder layer: error g_b [B][Co][2S][2S]
-// and layer input in_b [B][8][S][S] (both bf16).
-hipError_t conv_weight_grad(fire_nn *nn, const uint16_t *g_b, const uint16_t *in_b, int B, int Co,
-                            int S, float *dK, float *dkb, hipStream_t s) {
-  const int parts = B < 512 ? B : 512;
-  const int O = 2 * S;
-  const size_t lds = sizeof(uint16_t) * ((size_t)(Co * O * O + 7) / 8 * 8 + (size_t)kD0C * S * S);
-  hipLaunchKernelGGL(upconv_wgrad_mfma_kernel, dim3(parts), dim3(256), lds, s, g_b, in_b, B, S, Co,
+// Kernel and bias gradients of one decoder layer: error g_b [B][2S][2S][8] and
+// layer input in_b (both bf16).
+template <int S, bool PLANAR_IN>
+hipError_t conv_weight_grad(fire_nn *nn, const uint16_t *g_b, const uint16_t *in_b, int B, float *dK,
+                            float *dkb, hipStream_t s) {
+  const int64_t items = (int64_t)B * (2 * S / 32);
+  const int parts = (int)(items < kConvGrid ? items : kConvGrid);
+  hipLaunchKernelGGL((upconv_wgrad_kernel<S, PLANAR_IN>), dim3(parts), dim3(256), 0, s, g_b, in_b, B,
                      nn->wpart);
-  hipLaunchKernelGGL(wgrad_finish_kernel, dim3(Co * (kConvK + 1)), dim3(256), 0, s, nn->wpart,
-                     parts, Co, dK, dkb);
+  hipLaunchKernelGGL(wgrad_finish_kernel, dim3(kConvCi * (kConvK + 1)), dim3(256), 0, s, nn->wpart,
+                     parts, kConvCi, dK, dkb);
   return hipGetLastError();
 }
 
@@ -1143,33 +1264,32 @@ hipError_t backward(fire_nn *nn, const float *y_t, const uint8_t *y_map, int B, 
   const int64_t nz = (int64_t)B * kP;
   const bool use_map = y_map != nullptr && nn->cfg.w_map > 0.0f;
   if (use_map) {
-    const int nb = 1024;
-    hipLaunchKernelGGL(loss_map_kernel, dim3(nb), dim3(256), 0, s, nn->z, y_map, nz,
-                       nn->cfg.w_map, nn->gz, nn->partial);
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, nn->partial, nb,
-                       1.0f / (float)nz, nn->loss + 1);
+    hipLaunchKernelGGL((last_layer_kernel<true>), dim3(kLastBands * B), dim3(256), 0, s, nn->d2b, wb + L.K3.off,
+                       nn->w + L.k3.off, y_map, nn->cfg.w_map, 1.0f / (float)nz, nn->gzb, nn->partial,
+                       nullptr);
+    hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, s, nn->partial,
+                       B * kLastBands, 1.0f / (float)nz, nn->loss + 1);
     // decoder backward: each layer's error enters its two MFMA products as
     // bf16; the data gradient comes back summed over the 2x2 upsampling
-    // blocks and masked by the layer input's ReLU
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(nz)), dim3(256), 0, s, nn->gz, nn->gzb, nz);
-    // last layer (one output channel): kernel, bias and data gradients from
+    // blocks and masked by the layer input's ReLU.
+    // Last layer (one output channel): kernel, bias and data gradients from
     // the same 2x2 box sums of the error
     {
       const int64_t blocks = ((int64_t)B * 64 * 32 + 255) / 256;
-      const int parts = (int)(blocks < kWgradParts ? blocks : kWgradParts);
-      hipLaunchKernelGGL(upconv_grads_co1_kernel, dim3(parts), dim3(256), 0, s, nn->gzb,
-                         nn->d2b, B, 64, nn->wpart, wb + L.K3.off, nn->d2, nn->gd2, nn->gd2b);
+      const int parts = (int)(blocks < kCo1Grid ? blocks : kCo1Grid);
+      hipLaunchKernelGGL(upconv_grads_co1_kernel, dim3(parts), dim3(256), 0, s, nn->gzb, nn->d2b, B, 64,
+                         nn->wpart, wb + L.K3.off, nn->gd2b);
       hipLaunchKernelGGL(wgrad_finish_kernel, dim3(kConvK + 1), dim3(256), 0, s, nn->wpart, parts,
                          1, g + L.K3.off, g + L.k3.off);
     }
-    if ((e = conv_weight_grad(nn, nn->gd2b, nn->d1b, B, kD0C, 32, g + L.K2.off, g + L.k2.off, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL((upconv_mfma_kernel<false>), dim3(B), dim3(256), conv_lds(kD0C, 64), s,
-                       nn->gd2b, wb + L.K2.off, nullptr, 32, kD0C, 0, nn->d1, nn->gd1, nn->gd1b);
-    if ((e = conv_weight_grad(nn, nn->gd1b, nn->d0b, B, kD0C, 16, g + L.K1.off, g + L.k1.off, s)) != hipSuccess) return e;
+    if ((e = conv_weight_grad<32, false>(nn, nn->gd2b, nn->d1b, B, g + L.K2.off, g + L.k2.off, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL((upconv_dgrad_kernel<32, false>), dim3(4 * B), dim3(256), 0, s, nn->gd2b,
+                       wb + L.K2.off, nn->d1b, nn->gd1b, nullptr);
+    if ((e = conv_weight_grad<16, true>(nn, nn->gd1b, nn->d0b, B, g + L.K1.off, g + L.k1.off, s)) != hipSuccess) return e;
     // the last data gradient's bf16 copy replaces d0b, which the dense
     // layer's gradient products read next
-    hipLaunchKernelGGL((upconv_mfma_kernel<false>), dim3(B), dim3(256), conv_lds(kD0C, 32), s,
-                       nn->gd1b, wb + L.K1.off, nullptr, 16, kD0C, 0, nn->d0, nn->gd0, nn->d0b);
+    hipLaunchKernelGGL((upconv_dgrad_kernel<16, true>), dim3(2 * B), dim3(256), 0, s, nn->gd1b,
+                       wb + L.K1.off, nn->d0b, nn->d0b, nn->gd0);
     // dense decoder layer: gd0 already carries the ReLU mask of d0
     if ((e = gemm(kH, kDec, B, nn->h3b, 1, kH, nn->d0b, kDec, 1, g + L.Wd.off, kDec, nullptr, 0,
                   0, nullptr, s)) != hipSuccess) return e;
@@ -1245,33 +1365,16 @@ fire_status fire_nn_create(int device, const fire_nn_cfg *cfg, uint64_t seed, fi
   if (e == hipSuccess) e = nn_alloc(nn, &nn->dtb, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->ghb, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->t, Bm);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->d0, Bm * kDec);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->d1, Bm * kD0C * 32 * 32);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->d2, Bm * kD0C * 64 * 64);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->z, Bm * kP);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gt, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gd0, Bm * kDec);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->gd1, Bm * kD0C * 32 * 32);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->gd2, Bm * kD0C * 64 * 64);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->gz, Bm * kP);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gh, Bm * kH);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->partial, (int64_t)1024);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->partial, Bm * kLastBands);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->wpart, (int64_t)kWgradParts * kWgradRows * kWgradCols);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d1b, Bm * kD0C * 32 * 32);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d2b, Bm * kD0C * 64 * 64);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gzb, Bm * kP);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gd1b, Bm * kD0C * 32 * 32);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gd2b, Bm * kD0C * 64 * 64);
-  // the decoder kernels stage up to 96 KiB of planes in LDS
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&upconv_wgrad_mfma_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&upconv_mfma_kernel<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&upconv_mfma_kernel<false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->loss, 2);
   if (e != hipSuccess) return fail_out(e);
   // initial parameters
@@ -1338,8 +1441,9 @@ fire_status fire_nn_forward(fire_nn *nn, const float *x, int32_t B, float *out_t
   hipStream_t s = (hipStream_t)stream;
   NN_HIP(nn, forward(nn, x, B, s, out_map != nullptr, false, out_t));
   if (out_map) {
-    hipLaunchKernelGGL(sigmoid_kernel, dim3(blocks_for((int64_t)B * kP)), dim3(256), 0, s, nn->z,
-                       out_map, (int64_t)B * kP);
+    hipLaunchKernelGGL((last_layer_kernel<false>), dim3(kLastBands * B), dim3(256), 0, s,
+                       nn->d2b, nn->wb + nn->L.K3.off, nn->w + nn->L.k3.off, nullptr, 0.0f, 0.0f,
+                       nullptr, nullptr, out_map);
     NN_HIP(nn, hipGetLastError());
   }
   return FIRE_OK;

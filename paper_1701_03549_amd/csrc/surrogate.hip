@@ -1,7 +1,8 @@
 // Learned surrogate of the fire simulator (include/fire_nn.h): bf16 GEMMs on
 // MFMA (v_mfma_f32_32x32x16_bf16, fp32 accumulation) for the MLP and the
-// decoder's dense layer, fp32 upsample+3x3-convolution layers for the
-// decoder, fused losses, Adam with fp32 master weights.
+// decoder's dense layer, banded upsample+3x3-convolution layers on MFMA (the
+// last one, of one channel, on VALU) with bf16 cells between them, fused
+// losses, Adam with fp32 master weights.
 
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -25,6 +26,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
+}
+
+__device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+__device__ __forceinline__ float bf16_lo(uint32_t d) { return __uint_as_float(d << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t d) { return __uint_as_float(d & 0xFFFF0000u); }
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
 }
 
 int blocks_for(int64_t n, int t = 256) {
@@ -116,47 +124,80 @@ __device__ __forceinline__ void tile_store(uint16_t *S, int t, const uint16_t v[
   }
 }
 
+// One problem of a launch: C = op(A) op(B) (+ bias) (+ C), C or Cb may be NULL.
+struct GemmArgs {
+  int M, N, K;
+  const uint16_t *A;
+  int64_t sam, sak;
+  const uint16_t *B;
+  int64_t sbk, sbn;
+  float *C;
+  int64_t ldc;
+  const float *bias;
+  int relu, accumulate;
+  uint16_t *Cb;
+};
+// The problems of a launch, which fill the chip together: problem p's tiles
+// are blocks first[p] .. first[p + 1] - 1. The five weight gradients over 512
+// rows (168 workgroups): 18.6 us, after 81 us for five launches of 4 to 128.
+constexpr int kMaxGemms = 5;
+struct GemmBatch {
+  GemmArgs p[kMaxGemms];
+  int first[kMaxGemms + 1];
+};
+
+// kStages tiles of kTK per LDS buffer: their loads are in flight together, so
+// a workgroup waits for memory once in 64 k (a weight gradient over 512 rows
+// took 16 waits of about 1.1 us with one tile a buffer).
+constexpr int kStages = 2;
+
 template <int AM, int BM>
-__global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const uint16_t *A,
-                                                   int64_t sam, int64_t sak, const uint16_t *B,
-                                                   int64_t sbk, int64_t sbn, float *C,
-                                                   int64_t ldc, const float *bias, int relu,
-                                                   int accumulate, uint16_t *Cb) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][kTM * kLdt];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kTN * kLdt];
+__device__ __forceinline__ void gemm_tile(const GemmArgs &q, int tile) {
+  __shared__ __attribute__((aligned(16))) uint16_t As[2][kStages][kTM * kLdt];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kStages][kTN * kLdt];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m0 = blockIdx.y * kTM, n0 = blockIdx.x * kTN;
+  const int nt = (q.N + kTN - 1) / kTN;
+  const int m0 = tile / nt * kTM, n0 = tile % nt * kTN;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   f32x16_t acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  uint16_t va[8], vb[8];
-  tile_load<AM>(A, sam, sak, m0, M, 0, K, tid, va);
-  tile_load<BM>(B, sbn, sbk, n0, N, 0, K, tid, vb);
-  tile_store<AM>(As[0], tid, va);
-  tile_store<BM>(Bs[0], tid, vb);
+  uint16_t va[kStages][8], vb[kStages][8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < kStages; ++j) {
+      tile_load<AM>(q.A, q.sam, q.sak, m0, q.M, k0 + j * kTK, q.K, tid, va[j]);
+      tile_load<BM>(q.B, q.sbn, q.sbk, n0, q.N, k0 + j * kTK, q.K, tid, vb[j]);
+    }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < kStages; ++j) {
+      tile_store<AM>(As[buf][j], tid, va[j]);
+      tile_store<BM>(Bs[buf][j], tid, vb[j]);
+    }
+  };
+  load(0);
+  store(0);
   __syncthreads();
   const int half = lane >> 5, r = lane & 31;
   int buf = 0;
-  for (int k0 = 0; k0 < K; k0 += kTK) {
-    const bool more = k0 + kTK < K;
-    if (more) {
-      tile_load<AM>(A, sam, sak, m0, M, k0 + kTK, K, tid, va);
-      tile_load<BM>(B, sbn, sbk, n0, N, k0 + kTK, K, tid, vb);
-    }
+  for (int k0 = 0; k0 < q.K; k0 += kStages * kTK) {
+    const bool more = k0 + kStages * kTK < q.K;
+    if (more) load(k0 + kStages * kTK);
 #pragma unroll
-    for (int kk = 0; kk < kTK; kk += 16) {
-      const bf16x8_t a =
-          *reinterpret_cast<const bf16x8_t *>(&As[buf][(wr + r) * kLdt + kk + half * 8]);
-      const bf16x8_t b =
-          *reinterpret_cast<const bf16x8_t *>(&Bs[buf][(wc + r) * kLdt + kk + half * 8]);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+    for (int j = 0; j < kStages; ++j) {
+      if (k0 + j * kTK >= q.K) break;
+#pragma unroll
+      for (int kk = 0; kk < kTK; kk += 16) {
+        const bf16x8_t a =
+            *reinterpret_cast<const bf16x8_t *>(&As[buf][j][(wr + r) * kLdt + kk + half * 8]);
+        const bf16x8_t b =
+            *reinterpret_cast<const bf16x8_t *>(&Bs[buf][j][(wc + r) * kLdt + kk + half * 8]);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+      }
     }
-    if (more) {
-      // the other buffer was last read before the previous barrier
-      tile_store<AM>(As[buf ^ 1], tid, va);
-      tile_store<BM>(Bs[buf ^ 1], tid, vb);
-    }
+    if (more) store(buf ^ 1);  // last read before the previous barrier
     __syncthreads();
     buf ^= 1;
   }
@@ -165,15 +206,48 @@ __global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, const ui
     const int i = wr + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
     const int j = wc + (lane & 31);
     const int m = m0 + i, n = n0 + j;
-    if (m < M && n < N) {
+    if (m < q.M && n < q.N) {
       float val = acc[v];
-      if (bias) val += bias[n];
-      if (accumulate) val += C[(int64_t)m * ldc + n];  // (C is given)
-      if (relu) val = fmaxf(val, 0.0f);
-      if (C) C[(int64_t)m * ldc + n] = val;
-      if (Cb) Cb[(int64_t)m * ldc + n] = f2bf(val);
+      if (q.bias) val += q.bias[n];
+      if (q.accumulate) val += q.C[(int64_t)m * q.ldc + n];
+      if (q.relu) val = fmaxf(val, 0.0f);
+      if (q.C) q.C[(int64_t)m * q.ldc + n] = val;
+      if (q.Cb) q.Cb[(int64_t)m * q.ldc + n] = f2bf(val);
     }
   }
+}
+
+template <int AM, int BM>
+__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs q) {
+  gemm_tile<AM, BM>(q, blockIdx.x);
+}
+
+template <int AM, int BM>
+__global__ __launch_bounds__(256) void gemm_batch_kernel(GemmBatch batch) {
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < kMaxGemms; ++k) i += (int)blockIdx.x >= batch.first[k] ? 1 : 0;
+  gemm_tile<AM, BM>(batch.p[i], (int)blockIdx.x - batch.first[i]);
+}
+
+int64_t gemm_tiles(const GemmArgs &q) {
+  return (int64_t)((q.M + kTM - 1) / kTM) * ((q.N + kTN - 1) / kTN);
+}
+
+// n problems in one launch, every operand with load mode AM, BM
+template <int AM, int BM>
+hipError_t gemm_batch(const GemmArgs *q, int n, hipStream_t s) {
+  GemmBatch batch{};
+  int at = 0;
+  for (int i = 0; i < kMaxGemms; ++i) {
+    batch.first[i] = i < n ? at : 0x7FFFFFFF;
+    if (i < n) {
+      batch.p[i] = q[i];
+      at += (int)gemm_tiles(q[i]);
+    }
+  }
+  hipLaunchKernelGGL((gemm_batch_kernel<AM, BM>), dim3(at), dim3(256), 0, s, batch);
+  return hipGetLastError();
 }
 
 // how an operand of `rows` x `kdim` with strides (sr, sk) is loaded
@@ -185,34 +259,22 @@ int load_mode(const uint16_t *p, int64_t sr, int64_t sk) {
 }
 
 template <int AM>
-hipError_t gemm_b(int bm, dim3 grid, hipStream_t s, int M, int N, int K, const uint16_t *A,
-                  int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk, int64_t sbn, float *C,
-                  int64_t ldc, const float *bias, int relu, int accumulate, uint16_t *Cb) {
-  if (bm == kAlongK)
-    hipLaunchKernelGGL((gemm_kernel<AM, kAlongK>), grid, dim3(256), 0, s, M, N, K, A, sam, sak,
-                       B, sbk, sbn, C, ldc, bias, relu, accumulate, Cb);
-  else if (bm == kAlongRows)
-    hipLaunchKernelGGL((gemm_kernel<AM, kAlongRows>), grid, dim3(256), 0, s, M, N, K, A, sam,
-                       sak, B, sbk, sbn, C, ldc, bias, relu, accumulate, Cb);
-  else
-    hipLaunchKernelGGL((gemm_kernel<AM, kElementwise>), grid, dim3(256), 0, s, M, N, K, A, sam,
-                       sak, B, sbk, sbn, C, ldc, bias, relu, accumulate, Cb);
+hipError_t gemm_b(int bm, const GemmArgs &q, hipStream_t s) {
+  const dim3 grid((unsigned)gemm_tiles(q));
+  if (bm == kAlongK) hipLaunchKernelGGL((gemm_kernel<AM, kAlongK>), grid, dim3(256), 0, s, q);
+  else if (bm == kAlongRows) hipLaunchKernelGGL((gemm_kernel<AM, kAlongRows>), grid, dim3(256), 0, s, q);
+  else hipLaunchKernelGGL((gemm_kernel<AM, kElementwise>), grid, dim3(256), 0, s, q);
   return hipGetLastError();
 }
 
 hipError_t gemm(int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak,
                 const uint16_t *B, int64_t sbk, int64_t sbn, float *C, int64_t ldc,
                 const float *bias, int relu, int accumulate, uint16_t *Cb, hipStream_t s) {
-  dim3 grid((N + kTN - 1) / kTN, (M + kTM - 1) / kTM);
+  const GemmArgs q{M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, relu, accumulate, Cb};
   const int am = load_mode(A, sam, sak), bm = load_mode(B, sbn, sbk);
-  if (am == kAlongK)
-    return gemm_b<kAlongK>(bm, grid, s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, relu,
-                           accumulate, Cb);
-  if (am == kAlongRows)
-    return gemm_b<kAlongRows>(bm, grid, s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, relu,
-                              accumulate, Cb);
-  return gemm_b<kElementwise>(bm, grid, s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, relu,
-                              accumulate, Cb);
+  if (am == kAlongK) return gemm_b<kAlongK>(bm, q, s);
+  if (am == kAlongRows) return gemm_b<kAlongRows>(bm, q, s);
+  return gemm_b<kElementwise>(bm, q, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -228,6 +290,9 @@ hipError_t gemm(int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak
 // five launches of 8 to 32 workgroups and a copy.
 constexpr int kMlpH = 256, kMlpIn = 16, kMlpRows = 32, kMlpLd = kMlpH + 8;
 constexpr int kMlpThreads = 512;
+// parts of the contraction over the decoder's 2048 in the error of h3, each its
+// own tiles of the launch (four times the 32 workgroups of 512 rows)
+constexpr int kDhParts = 4;
 
 // acc += act[32][K] times the wave's 32 columns of w ([256][K] transposed
 // weights, w at the wave's first column's row)
@@ -329,18 +394,20 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_forward_kernel(
 // ---------------------------------------------------------------------------
 // Elementwise and reduction kernels
 
-// Where the transposed bf16 copy `wt` holds parameter i: W1, W2, W3 as
-// [out][in], then Wf; -1 for the others. off: the first elements of W1, W2,
-// W3 and Wf in the flat order.
+// Where the second bf16 copy `wt` holds parameter i: W1, W2, W3 as [out][in],
+// then Wf and Wd as they are, but on 16-byte boundaries (Wd's first element is
+// an odd one in the flat order); -1 for the others. off: the first elements of
+// W1, W2, W3, Wf and Wd in the flat order.
 struct MlpOffsets {
-  int64_t w1, w2, w3, wf;
+  int64_t w1, w2, w3, wf, wd, wd_n;
 };
 __device__ __forceinline__ int64_t wt_index(const MlpOffsets &o, int64_t i) {
   constexpr int64_t kIn = kMlpIn * kMlpH, kSq = kMlpH * kMlpH;
   if (i < o.w1 + kIn) return i < o.w1 ? -1 : (i - o.w1) % kMlpH * kMlpIn + (i - o.w1) / kMlpH;
   if (i < o.w2 + kSq) return i < o.w2 ? -1 : kIn + (i - o.w2) % kMlpH * kMlpH + (i - o.w2) / kMlpH;
   if (i < o.w3 + kSq) return i < o.w3 ? -1 : kIn + kSq + (i - o.w3) % kMlpH * kMlpH + (i - o.w3) / kMlpH;
-  return i >= o.wf && i < o.wf + kMlpH ? kIn + 2 * kSq + (i - o.wf) : -1;
+  if (i < o.wf + kMlpH) return i < o.wf ? -1 : kIn + 2 * kSq + (i - o.wf);
+  return i >= o.wd && i < o.wd + o.wd_n ? kIn + 2 * kSq + kMlpH + (i - o.wd) : -1;
 }
 
 // the bf16 copies of the master weights
@@ -355,29 +422,129 @@ __global__ void refresh_weights_kernel(const float *w, uint16_t *wb, uint16_t *w
   }
 }
 
-// g <- g * (h > 0) (ReLU backward, in place; h the bf16 activations) and its
-// bf16 copy
-__global__ void relu_bwd_kernel(float *g, const uint16_t *h, uint16_t *gb, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const float v = (h[i] & 0x7FFFu) != 0 ? g[i] : 0.0f;  // (a ReLU's output is not negative)
-    g[i] = v;
-    gb[i] = f2bf(v);
+// The MLP's error chain in one launch, 32 rows a workgroup as in the forward
+// pass: e3 = dt Wf^T + the kDhParts parts of dd0 Wd^T (dh, NULL without maps),
+// e2 = e3' W3^T, e1 = e2' W2^T, each masked by its layer's ReLU (h the bf16
+// activations), to g (fp32, for the bias gradients) and gb (bf16, what the next
+// product and the weight gradients read). W3 and W2 are read along their rows,
+// which is along k here. Bound, as the forward pass, by the chain itself (16
+// workgroups at 512 rows): 15.5 us at 512 rows with every mask and error loaded
+// ahead (41 us with a branch per row), after 86 us for three ReLU passes, two
+// products, the rank-one product and an accumulating one over 2048.
+__global__ __launch_bounds__(kMlpThreads) void mlp_backward_kernel(
+    const uint16_t *dtb, const float *dh, int64_t part_stride, int B, const uint16_t *wf,
+    const uint16_t *w3, const uint16_t *w2, const uint16_t *h3b, const uint16_t *h2b,
+    const uint16_t *h1b, float *g3, float *g2, float *g1, uint16_t *gb3, uint16_t *gb2, uint16_t *gb1) {
+  __shared__ __attribute__((aligned(16))) uint16_t act[2][kMlpRows * kMlpLd];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = blockIdx.x * kMlpRows, col = 32 * wave + (lane & 31);
+  uint4 w[16];
+  mlp_load<kMlpH>(w3 + 32 * wave * kMlpH, lane, w);
+  // this lane's outputs of a layer: rows row(v), column col. Loads take the
+  // last row in place of the rows past it, so that none waits for a branch.
+  auto row = [&](int v) { return row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
+  auto mask_load = [&](const uint16_t *h, uint16_t (&m)[16]) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) m[v] = h[(int64_t)min(row(v), B - 1) * kMlpH + col];
+  };
+  uint16_t m2[16], m1[16];
+  mask_load(h2b, m2);
+  constexpr int kQuads = kMlpRows * kMlpH / 4 / kMlpThreads;
+  const int n = tid % (kMlpH / 4) * 4, r0 = tid / (kMlpH / 4);
+  float4 d[kQuads];
+  uint2 m3[kQuads];
+  float dt[kQuads];
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) {
+    const int b = min(row0 + r0 + i * (kMlpRows / kQuads), B - 1);
+    const int64_t o = (int64_t)b * kMlpH + n;
+    dt[i] = bf16_f32(dtb[b]);
+    m3[i] = *reinterpret_cast<const uint2 *>(h3b + o);
+    d[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (dh) {
+      d[i] = *reinterpret_cast<const float4 *>(dh + o);
+#pragma unroll
+      for (int k = 1; k < kDhParts; ++k) {
+        const float4 q = *reinterpret_cast<const float4 *>(dh + k * part_stride + o);
+        d[i].x += q.x;
+        d[i].y += q.y;
+        d[i].z += q.z;
+        d[i].w += q.w;
+      }
+    }
   }
+  const uint2 wq = *reinterpret_cast<const uint2 *>(wf + n);
+  const float wn[4] = {bf16_lo(wq.x), bf16_hi(wq.x), bf16_lo(wq.y), bf16_hi(wq.y)};
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) {
+    const int r = r0 + i * (kMlpRows / kQuads), b = row0 + r;
+    const float h[4] = {bf16_lo(m3[i].x), bf16_hi(m3[i].x), bf16_lo(m3[i].y), bf16_hi(m3[i].y)};
+    const float dd[4] = {d[i].x, d[i].y, d[i].z, d[i].w};
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = b < B && h[j] > 0.0f ? dd[j] + dt[i] * wn[j] : 0.0f;
+    const uint2 q = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    *reinterpret_cast<uint2 *>(&act[0][r * kMlpLd + n]) = q;
+    if (b < B) {
+      *reinterpret_cast<float4 *>(g3 + (int64_t)b * kMlpH + n) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<uint2 *>(gb3 + (int64_t)b * kMlpH + n) = q;
+    }
+  }
+  __syncthreads();
+  auto finish = [&](const f32x16_t &acc, const uint16_t (&m)[16], float *g, uint16_t *gb, uint16_t *to) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float val = row(v) < B && bf16_f32(m[v]) > 0.0f ? acc[v] : 0.0f;
+      const uint16_t q = f2bf(val);
+      if (to) to[(row(v) - row0) * kMlpLd + col] = q;
+      if (row(v) < B) {
+        const int64_t o = (int64_t)row(v) * kMlpH + col;
+        g[o] = val;
+        gb[o] = q;
+      }
+    }
+  };
+  const f32x16_t a2 = mlp_tile<kMlpH>(act[0], lane, w);
+  mlp_load<kMlpH>(w2 + 32 * wave * kMlpH, lane, w);
+  mask_load(h1b, m1);
+  finish(a2, m2, g2, gb2, act[1]);
+  __syncthreads();
+  finish(mlp_tile<kMlpH>(act[1], lane, w), m1, g1, gb1, nullptr);
 }
 
 // column sums of d [M][N] (bias gradients) in a fixed order: a workgroup of
 // 256 threads takes 16 columns; row group r (0..15) sums rows r, r+16, ...
-// in order, then the 16 partial sums are added pairwise:
-// p0+p1, p2+p3, ..., then those pairwise, down to one
-constexpr int kColsumCols = 16, kColsumGroups = 16;
-__global__ __launch_bounds__(256) void colsum_kernel(const float *d, int M, int N, float *out) {
+// in order (eight loads in flight), then the 16 partial sums are added
+// pairwise: p0+p1, p2+p3, ..., then those pairwise, down to one. Several
+// matrices of M rows in one launch: matrix i has blocks first[i] .. The five
+// bias gradients over 512 rows: 4.9 us, after 51 us for five launches.
+constexpr int kColsumCols = 16, kColsumGroups = 16, kMaxColsums = 5;
+struct Colsums {
+  const float *d[kMaxColsums];
+  float *out[kMaxColsums];
+  int N[kMaxColsums], first[kMaxColsums];
+};
+__global__ __launch_bounds__(256) void colsum_kernel(Colsums q, int M) {
   __shared__ float part[kColsumGroups][kColsumCols];
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxColsums; ++i) k += (int)blockIdx.x >= q.first[i] ? 1 : 0;
+  const float *d = q.d[k];
+  const int N = q.N[k];
   const int c = threadIdx.x % kColsumCols, rg = threadIdx.x / kColsumCols;
-  const int n = blockIdx.x * kColsumCols + c;
+  const int n = ((int)blockIdx.x - q.first[k]) * kColsumCols + c;
   float s = 0.0f;
-  if (n < N)
-    for (int m = rg; m < M; m += kColsumGroups) s += d[(int64_t)m * N + n];
+  if (n < N) {
+    int m = rg;
+    for (; m + 7 * kColsumGroups < M; m += 8 * kColsumGroups) {
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = d[(int64_t)(m + j * kColsumGroups) * N + n];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s += v[j];
+    }
+    for (; m < M; m += kColsumGroups) s += d[(int64_t)m * N + n];
+  }
   part[rg][c] = s;
   __syncthreads();
   if (rg == 0 && n < N) {
@@ -388,11 +555,25 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float *d, int M, int 
     for (int w = kColsumGroups; w > 1; w >>= 1)
 #pragma unroll
       for (int i = 0; i < w / 2; ++i) p[i] = p[2 * i] + p[2 * i + 1];
-    out[n] = p[0];
+    q.out[k][n] = p[0];
   }
 }
 
-int colsum_blocks(int N) { return (N + kColsumCols - 1) / kColsumCols; }
+// the column sums of n matrices d[i] [M][N[i]] into out[i]
+hipError_t colsums(const float *const *d, const int *N, float *const *out, int n, int M, hipStream_t s) {
+  Colsums q{};
+  int at = 0;
+  for (int i = 0; i < kMaxColsums; ++i) {
+    q.first[i] = i < n ? at : 0x7FFFFFFF;
+    if (i >= n) continue;
+    q.d[i] = d[i];
+    q.out[i] = out[i];
+    q.N[i] = N[i];
+    at += (N[i] + kColsumCols - 1) / kColsumCols;
+  }
+  hipLaunchKernelGGL(colsum_kernel, dim3(at), dim3(256), 0, s, q, M);
+  return hipGetLastError();
+}
 
 __device__ float block_reduce(float v, float *red) {
   const int t = threadIdx.x;
@@ -467,12 +648,6 @@ constexpr int kWgradParts = 2048;
 constexpr int kConvGrid = 512, kCo1Grid = 1024;
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
-__device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-__device__ __forceinline__ float bf16_lo(uint32_t d) { return __uint_as_float(d << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t d) { return __uint_as_float(d & 0xFFFF0000u); }
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  return (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
-}
 
 // Cell (y, x) of a sample's [8][R][R] planes (PLANAR) or [R][R][8] cells.
 template <bool PLANAR>
@@ -1134,6 +1309,7 @@ using namespace firenn;
 namespace {
 constexpr int kH = 256, kIn = 16, kD0C = 8, kD0S = 16, kDec = kD0C * kD0S * kD0S;
 constexpr int kP = FIRE_NN_MAP * FIRE_NN_MAP;
+constexpr int64_t kWtWd = kIn * kH + 2 * kH * kH + kH;  // Wd in fire_nn::wt
 
 struct Seg {
   int64_t off, n;
@@ -1166,11 +1342,12 @@ struct fire_nn {
   Layout L;
   float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // [total]
   uint16_t *wb = nullptr;                                        // bf16 copy [total]
-  uint16_t *wt = nullptr;  // bf16 W1, W2, W3 transposed ([out][in]), Wf
+  uint16_t *wt = nullptr;  // bf16 W1, W2, W3 transposed ([out][in]), Wf, Wd
   // activations (max_batch rows)
   uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr, *h3b = nullptr, *d0b = nullptr, *dtb = nullptr;
   float *t = nullptr;
-  float *gt = nullptr, *gd0 = nullptr, *gh = nullptr;
+  // errors of h3, h2, h1 (gh fp32, ghb bf16) and the parts of dd0 Wd^T (dh)
+  float *gt = nullptr, *gd0 = nullptr, *gh = nullptr, *dh = nullptr;
   uint16_t *ghb = nullptr;
   // bf16 copies the decoder's MFMA convolutions read
   uint16_t *d1b = nullptr, *d2b = nullptr, *gzb = nullptr, *gd1b = nullptr, *gd2b = nullptr;
@@ -1204,7 +1381,9 @@ hipError_t nn_alloc(fire_nn *nn, T **p, int64_t count) {
   return e;
 }
 
-MlpOffsets mlp_offsets(const Layout &L) { return {L.W1.off, L.W2.off, L.W3.off, L.Wf.off}; }
+MlpOffsets mlp_offsets(const Layout &L) {
+  return {L.W1.off, L.W2.off, L.W3.off, L.Wf.off, L.Wd.off, L.Wd.n};
+}
 
 hipError_t refresh_bf16(fire_nn *nn, hipStream_t s) {
   hipLaunchKernelGGL(refresh_weights_kernel, dim3(blocks_for(nn->L.total)), dim3(256), 0, s, nn->w,
@@ -1229,7 +1408,7 @@ hipError_t forward(fire_nn *nn, const float *x, int B, hipStream_t s, bool want_
                      train ? nn->h2b : nullptr, train || want_map ? nn->h3b : nullptr, t);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (!want_map) return hipSuccess;
-  if ((e = gemm(B, kDec, kH, nn->h3b, kH, 1, wb + L.Wd.off, kDec, 1, nullptr, kDec, w + L.cd.off,
+  if ((e = gemm(B, kDec, kH, nn->h3b, kH, 1, wt + kWtWd, kDec, 1, nullptr, kDec, w + L.cd.off,
                 1, 0, nn->d0b, s)) != hipSuccess) return e;
   // decoder: d0b (the dense layer's output) -> d1b -> d2b
   hipLaunchKernelGGL((upconv_kernel<16, true>), dim3(B), dim3(256), 0, s, nn->d0b, wb + L.K1.off,
@@ -1290,44 +1469,41 @@ hipError_t backward(fire_nn *nn, const float *y_t, const uint8_t *y_map, int B, 
     // layer's gradient products read next
     hipLaunchKernelGGL((upconv_dgrad_kernel<16, true>), dim3(2 * B), dim3(256), 0, s, nn->gd1b,
                        wb + L.K1.off, nn->d0b, nn->d0b, nn->gd0);
-    // dense decoder layer: gd0 already carries the ReLU mask of d0
-    if ((e = gemm(kH, kDec, B, nn->h3b, 1, kH, nn->d0b, kDec, 1, g + L.Wd.off, kDec, nullptr, 0,
-                  0, nullptr, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(colsum_blocks(kDec)), dim3(256), 0, s, nn->gd0, B, kDec,
-                       g + L.cd.off);
+    // the decoder's part of the error of h3: dd0 Wd^T, in kDhParts parts
+    GemmArgs q[kDhParts];
+    constexpr int kPart = kDec / kDhParts;
+    for (int i = 0; i < kDhParts; ++i)
+      q[i] = GemmArgs{B, kH, kPart, nn->d0b + i * kPart, kDec, 1, nn->wt + kWtWd + i * kPart, 1, kDec,
+                      nn->dh + i * ((int64_t)B * kH), kH, nullptr, 0, 0, nullptr};
+    if ((e = gemm_batch<kAlongK, kAlongK>(q, kDhParts, s)) != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(fill_f32_kernel, dim3(1), dim3(64), 0, s, nn->loss + 1, 0.0f, (int64_t)1);
     const int64_t o = L.Wd.off, n = L.k3.off + L.k3.n - L.Wd.off;
     hipLaunchKernelGGL(fill_f32_kernel, dim3(blocks_for(n)), dim3(256), 0, s, g + o, 0.0f, n);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // fitness head
-  if ((e = gemm(kH, 1, B, nn->h3b, 1, kH, nn->dtb, 1, 1, g + L.Wf.off, 1, nullptr, 0, 0, nullptr,
-                s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(colsum_kernel, dim3(1), dim3(256), 0, s, nn->gt, B, 1, g + L.cf.off);
-  // dh3 = dt Wf^T (+ dd0 Wd^T)
-  if ((e = gemm(B, kH, 1, nn->dtb, 1, 1, wb + L.Wf.off, 1, 1, nn->gh, kH, nullptr, 0, 0, nullptr,
-                s)) != hipSuccess) return e;
-  if (use_map)
-    if ((e = gemm(B, kH, kDec, nn->d0b, kDec, 1, wb + L.Wd.off, 1, kDec, nn->gh, kH, nullptr, 0, 1,
-                  nullptr, s)) != hipSuccess) return e;
-  // through the three hidden layers
-  struct Lay { const uint16_t *in_b, *act; const Seg *W; const Seg *c; int kin; };
-  const Lay lays[3] = {{nn->h2b, nn->h3b, &L.W3, &L.c3, kH},
-                       {nn->h1b, nn->h2b, &L.W2, &L.c2, kH},
-                       {nn->xb, nn->h1b, &L.W1, &L.c1, kIn}};
-  for (int li = 0; li < 3; ++li) {
-    const Lay &ly = lays[li];
-    hipLaunchKernelGGL(relu_bwd_kernel, dim3(blocks_for((int64_t)B * kH)), dim3(256), 0, s, nn->gh,
-                       ly.act, nn->ghb, (int64_t)B * kH);
-    if ((e = gemm(ly.kin, kH, B, ly.in_b, 1, ly.kin, nn->ghb, kH, 1, g + ly.W->off, kH, nullptr, 0,
-                  0, nullptr, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(colsum_kernel, dim3(colsum_blocks(kH)), dim3(256), 0, s, nn->gh, B, kH,
-                       g + ly.c->off);
-    if (li < 2)
-      if ((e = gemm(B, kH, kH, nn->ghb, kH, 1, wb + ly.W->off, 1, kH, nn->gh, kH, nullptr, 0, 0,
-                    nullptr, s)) != hipSuccess) return e;
-  }
+  // the error chain through the hidden layers
+  const int64_t bh = (int64_t)B * kH;
+  float *g3 = nn->gh, *g2 = g3 + bh, *g1 = g2 + bh;
+  uint16_t *gb3 = nn->ghb, *gb2 = gb3 + bh, *gb1 = gb2 + bh;
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3((B + kMlpRows - 1) / kMlpRows), dim3(kMlpThreads), 0, s,
+                     nn->dtb, use_map ? nn->dh : nullptr, bh, B, nn->wt + kIn * kH + 2 * kH * kH,
+                     wb + L.W3.off, wb + L.W2.off, nn->h3b, nn->h2b, nn->h1b, g3, g2, g1, gb3, gb2, gb1);
+  // weight gradients (activations^T errors, over the batch) and bias gradients
+  // (column sums), each kind in one launch: alone, none of them fills the chip
+  const GemmArgs q[kMaxGemms] = {
+      {kH, kDec, B, nn->h3b, 1, kH, nn->d0b, kDec, 1, g + L.Wd.off, kDec, nullptr, 0, 0, nullptr},
+      {kH, kH, B, nn->h2b, 1, kH, gb3, kH, 1, g + L.W3.off, kH, nullptr, 0, 0, nullptr},
+      {kH, kH, B, nn->h1b, 1, kH, gb2, kH, 1, g + L.W2.off, kH, nullptr, 0, 0, nullptr},
+      {kIn, kH, B, nn->xb, 1, kIn, gb1, kH, 1, g + L.W1.off, kH, nullptr, 0, 0, nullptr},
+      // (one column: read element by element, as the ends of rows are)
+      {kH, 1, B, nn->h3b, 1, kH, nn->dtb, 1, 1, g + L.Wf.off, 1, nullptr, 0, 0, nullptr}};
+  const int skip = use_map ? 0 : 1;  // without maps the decoder's gradients are zero
+  if ((e = gemm_batch<kAlongRows, kAlongRows>(q + skip, kMaxGemms - skip, s)) != hipSuccess) return e;
+  const float *const sums[kMaxColsums] = {nn->gd0, g3, g2, g1, nn->gt};
+  const int cols[kMaxColsums] = {kDec, kH, kH, kH, 1};
+  float *const outs[kMaxColsums] = {g + L.cd.off, g + L.c3.off, g + L.c2.off, g + L.c1.off, g + L.cf.off};
+  if ((e = colsums(sums + skip, cols + skip, outs + skip, kMaxColsums - skip, B, s)) != hipSuccess) return e;
   return hipGetLastError();
 }
 }  // namespace
@@ -1356,18 +1532,19 @@ fire_status fire_nn_create(int device, const fire_nn_cfg *cfg, uint64_t seed, fi
   if (e == hipSuccess) e = nn_alloc(nn, &nn->v, T);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->g, T);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->wb, T);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->wt, kIn * kH + 2 * kH * kH + kH);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->wt, kWtWd + (int64_t)kH * kDec);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->xb, Bm * kIn);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->h1b, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->h2b, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->h3b, Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d0b, Bm * kDec);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->dtb, Bm);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->ghb, Bm * kH);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->ghb, 3 * Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->t, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gt, Bm);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->gd0, Bm * kDec);
-  if (e == hipSuccess) e = nn_alloc(nn, &nn->gh, Bm * kH);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->gh, 3 * Bm * kH);
+  if (e == hipSuccess) e = nn_alloc(nn, &nn->dh, kDhParts * Bm * kH);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->partial, Bm * kLastBands);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->wpart, (int64_t)kWgradParts * kWgradRows * kWgradCols);
   if (e == hipSuccess) e = nn_alloc(nn, &nn->d1b, Bm * kD0C * 32 * 32);
@@ -1511,9 +1688,7 @@ fire_status fire_pool_maps(const uint32_t *maps, int32_t n, int32_t W, int32_t H
 
 fire_status fire_colsum_f32(const float *d, int32_t M, int32_t N, float *out, void *stream) {
   if (!d || !out || M < 1 || N < 1) return FIRE_E_INVALID;
-  hipLaunchKernelGGL(colsum_kernel, dim3(colsum_blocks(N)), dim3(256), 0, (hipStream_t)stream, d,
-                     M, N, out);
-  return hipGetLastError() == hipSuccess ? FIRE_OK : FIRE_E_DEVICE;
+  return colsums(&d, &N, &out, 1, M, (hipStream_t)stream) == hipSuccess ? FIRE_OK : FIRE_E_DEVICE;
 }
 
 fire_status fire_nn_select(const double *cand, const float *score, int32_t n, int32_t G,

@@ -85,3 +85,31 @@ def test_decoder_bands_and_batches(B):
     z = S.forward(p, x[:n], 256, 256, bf16=True)["z"]
     assert np.allclose(maps.cpu().numpy().reshape(z.shape), 1 / (1 + np.exp(-z)), atol=2e-3)
     net.close()
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 33, 65])
+@pytest.mark.parametrize("use_map", [False, True])
+def test_hidden_layers_gradients_at_workgroup_edges(B, use_map):
+    """The error chain of the hidden layers and the launches that hold several
+    products or column sums, with and without the decoder's part: each of the
+    MLP's gradients against the binary64 reference with the same bf16 rounding
+    points."""
+    import torch
+    from paper_1701_03549_amd import nn
+    w_map = 0.5 if use_map else 0.0
+    net = nn.Surrogate(max_batch=65, lattice=(256, 256), w_map=w_map, seed=12)
+    x, y = _rows(B, 60 + B)
+    m = (np.random.default_rng(B).random((B, 128, 128)) < 0.2).astype(np.uint8)
+    _, g = net.gradients(torch.from_numpy(x), torch.from_numpy(y),
+                         torch.from_numpy(m).cuda() if use_map else None)
+    p = net.get_params().cpu().numpy().astype(np.float64)
+    _, _, ref = S.loss_and_grads(p, x, y, m, 256, 256, w_map, bf16=True)
+    got, want = S.unflatten(g.cpu().numpy().astype(np.float64)), S.unflatten(np.asarray(ref))
+    # an activation or error near a bf16 rounding point may round the other way
+    # (2^-8 of it): at most that of the norm in each of the chain's four layers
+    for name in ("W1", "c1", "W2", "c2", "W3", "c3", "Wf", "cf") + (("Wd", "cd") if use_map else ()):
+        err = np.linalg.norm(got[name] - want[name])
+        assert err <= 2.0 ** -6 * np.linalg.norm(want[name]), name
+    if not use_map:
+        assert all(not np.any(got[k]) for k in ("Wd", "cd", "K1", "k1", "K2", "k2", "K3", "k3"))
+    net.close()

@@ -33,7 +33,9 @@ struct LandscapeHost {
   // average over window runs; windows are not used while it exceeds
   // kWindowRetryMax)
   float win_frac = 0.f;
-  int win_obs = 0;
+  // the same for runs in the wide window that follows the first repeats
+  float wide_frac = 0.f;
+  int win_obs = 0, wide_obs = 0;
   // landscape means for ordering simulations by expected fire size: share
   // of forest among burnable cells, mean psi, mean sigma of an edge, and
   // the number of burnable cells
@@ -74,6 +76,7 @@ struct fire_ctx {
   hipEvent_t stat_ev[kStatSlots] = {};
   int stat_ls[kStatSlots] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
   int stat_n[kStatSlots] = {};
+  bool stat_wide[kStatSlots] = {};
   // workgroups of each simulation-kernel variant resident per CU as far as
   // registers allow ([threads 64..1024][table][turn-off times][window];
   // 0 = unknown)
@@ -381,6 +384,7 @@ struct RunPlan {
   // reaches the window edge run again in a second launch over the whole
   // lattice, with the plan below.
   int win;
+  bool wide = false;  // `win` is the wide window (kWidePerCu workgroups a compute unit)
   fire_schedule s2;
   int bitset_words2;
   size_t lds2;
@@ -391,6 +395,19 @@ struct RunPlan {
 // repeat a simulation: the repeats run after the window launch, so even a
 // few of them cost a whole simulation's latency.
 constexpr float kWindowRetryMax = 0.0f;
+// The wide window. A lattice whose bitset takes more than half of the LDS has
+// one whole-lattice workgroup per compute unit, whose lanes a front of some
+// hundred cells leaves mostly idle. After the first repeats, replicate batches
+// run there in the largest window that keeps kWidePerCu workgroups of
+// kWideThreads resident with kWideQueue entries each (640 cells a side), if the
+// batch has more simulations than these (so that the first window, which kept
+// more resident, was smaller) and unless more than kWideRetryMax of such a run had to
+// be repeated: a repeat costs what its simulation would have cost at first.
+// 8192 simulations of the 1024x1024 ignition scan: 4.8 ms whole-lattice, 3.1 ms
+// in the wide window (128 threads 3.8, 512 threads 3.6 ms; 704 cells a side,
+// two workgroups, 3.8 ms).
+constexpr int kWidePerCu = 3, kWideThreads = 256, kWideQueue = 256;
+constexpr float kWideRetryMax = 0.25f;
 constexpr int kMinAutoQueue = 1024;      // LDS queue entries a built-in window should leave
 // Built-in windows only for batches of replicates (at most this many
 // parameter vectors): with many different vectors (a GA population, Monte
@@ -435,10 +452,11 @@ int batch_kind(int32_t n_params, int32_t n_sims) {
 
 // Launch plan for simulations on landscapes of at most max_h rows of
 // max_stride bitset words (bitset_words = the largest H * stride) and
-// max_cells cells.
+// max_cells cells. wide_frac: the repeated share of runs in the wide window (1:
+// no such window, for callers whose buffers are sized by an earlier plan).
 fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h,
                      int max_stride, int32_t n_params, int32_t n_sims, bool table_allowed,
-                     RunPlan *out, bool dur = false, float win_frac = 0.f) {
+                     RunPlan *out, bool dur = false, float win_frac = 0.f, float wide_frac = 1.f) {
   fire_schedule s = default_schedule(c, max_cells, bitset_words, n_params, dur, n_sims);
   s.window = -1;  // built-in: decide below
   s.wave = -1;
@@ -486,6 +504,7 @@ fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h
   out->lds = lds;
   out->grid = grid;
   out->win = 0;
+  out->wide = false;
   // window: asked for by the schedule, or (built-in) the largest one that
   // keeps as many simulations of the batch resident as any window can, when
   // that is more than whole-lattice bitsets allow and recent window runs on
@@ -598,11 +617,27 @@ fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h
       }
     }
   }
-  if (win <= 0 || window_words(win) >= bitset_words) return FIRE_OK;
   fire_schedule ws;
   size_t wlds = 0;
   int wgrid = 0;
-  if (!shape_for(win, ws, &wlds, &wgrid)) return FIRE_OK;
+  bool wide = false;
+  if (s.window < 0 && win_frac > kWindowRetryMax && wide_frac <= kWideRetryMax &&
+      n_params <= kWindowMaxParams && !gb && grid <= c->num_cu &&
+      n_sims > kWidePerCu * c->num_cu) {
+    const int64_t words = (int64_t)(c->max_lds / kWidePerCu - kLdsMargin) / 4 - 16 - 2 * kWideQueue;
+    for (int side = (std::max(max_h, 32 * max_stride) - 1) / 32 * 32; side >= 64 && win == 0; side -= 32)
+      if (window_words(side) <= words) win = side;
+    ws = full;
+    ws.threads = kWideThreads;
+    ws.queue_cap = queue_cap_for(c->max_lds / kWidePerCu - kLdsMargin, window_words(win), dur);
+    ws.wg_per_cu = kWidePerCu;
+    wide = win > 0 && ws.queue_cap >= 64 &&
+           shape_launch(c, ws, window_words(win), dur, true, n_sims, &wlds, &wgrid) &&
+           wgrid > grid;
+    if (!wide) return FIRE_OK;
+  }
+  if (win <= 0 || window_words(win) >= bitset_words) return FIRE_OK;
+  if (!wide && !shape_for(win, ws, &wlds, &wgrid)) return FIRE_OK;
   // window runs only with kernel variants that keep their registers (the
   // spilling variants are slow enough that residency gains nothing)
   if (sim_scratch_bytes(ws.threads, ws.table_mode != 0, dur, true) > 0) return FIRE_OK;
@@ -621,6 +656,7 @@ fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h
   out->lds = wlds;
   out->grid = wgrid;
   out->win = win;
+  out->wide = wide;
   return FIRE_OK;
 }
 
@@ -681,8 +717,13 @@ void harvest_stats(fire_ctx *c) {
     if (l < (int)c->ls.size() && c->ls[l].live && c->stat_n[i] > 0) {
       LandscapeHost &L = c->ls[l];
       const float f = (float)c->h_stat[i] / (float)c->stat_n[i];
-      L.win_frac = L.win_obs ? 0.5f * L.win_frac + 0.5f * f : f;
-      ++L.win_obs;
+      if (c->stat_wide[i]) {
+        L.wide_frac = L.wide_obs ? 0.5f * L.wide_frac + 0.5f * f : f;
+        ++L.wide_obs;
+      } else {
+        L.win_frac = L.win_obs ? 0.5f * L.win_frac + 0.5f * f : f;
+        ++L.win_obs;
+      }
     }
     c->stat_ls[i] = -1;
   }
@@ -774,6 +815,7 @@ fire_status launch_run(fire_ctx *c, const RunPlan &p, const double *betas_dev,
       if (hipEventRecord(c->stat_ev[slot], st) == hipSuccess) {
         c->stat_ls[slot] = stat_lid;
         c->stat_n[slot] = n_sims;
+        c->stat_wide[slot] = p.wide;
       } else {
         (void)hipGetLastError();
       }
@@ -1024,8 +1066,8 @@ fire_status fire_landscape_set_burn_steps(fire_ctx *c, int32_t id, const uint8_t
   HIP_OR_FAIL(c, hipSetDevice(c->device));
   HIP_OR_FAIL(c, hipDeviceSynchronize());
   LandscapeHost &L = c->ls[id];
-  L.win_frac = 0.f;  // fire sizes change with the turn-off times
-  L.win_obs = 0;
+  L.win_frac = L.wide_frac = 0.f;  // fire sizes change with the turn-off times
+  L.win_obs = L.wide_obs = 0;
   const int64_t n = (int64_t)L.W * L.H;
   if (!steps || all_one) {
     if (L.burn_steps) HIP_OR_FAIL(c, hipFree(L.burn_steps));
@@ -1285,7 +1327,7 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
   std::vector<int> ls_ids;
   for (int32_t i = 0; i < n_sims; ++i) {
     const int l = sims[i].landscape_id;
-    if (cls_of_ls[l] < 0) { cls_of_ls[l] = -2; ls_ids.push_back(l); }
+    if (cls_of_ls[l] == -1) { cls_of_ls[l] = -2; ls_ids.push_back(l); }
   }
   const bool per_ls = (int)ls_ids.size() <= kMaxClasses && !(lpt && ls_ids.size() > 1);
   if (per_ls) {
@@ -1334,17 +1376,18 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
   std::vector<RunPlan> plans(n_cls);
   int64_t spill_total = 0;
   harvest_stats(c);
-  std::vector<float> cls_frac(n_cls, 0.f);
+  std::vector<float> cls_frac(n_cls, 0.f), cls_wide(n_cls, 0.f);
   std::vector<int> cls_lid(n_cls, -1);
   for (int l : ls_ids) {
     const int k = cls_of_ls[l];
     cls_frac[k] = std::max(cls_frac[k], c->ls[l].win_frac);
+    cls_wide[k] = std::max(cls_wide[k], c->ls[l].wide_frac);
     cls_lid[k] = per_ls ? l : -1;
   }
   for (int k = 0; k < n_cls; ++k) {
     fire_status ps = plan_run(c, cls_words[k], cls_cells[k], cls_h[k], cls_stride[k], n_params,
                               (int32_t)members[k].size(), one_ls >= 0, &plans[k],
-                              cls_dur[k] != 0, cls_frac[k]);
+                              cls_dur[k] != 0, cls_frac[k], cls_wide[k]);
     if (ps != FIRE_OK) return ps;
     spill_total += spill_words(plans[k]);
   }
@@ -1453,7 +1496,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
   int bw = 0, nlive = 0, lid = -1, mh = 1, ms = 1;
   int64_t mc = 1;
   bool any_dur = false;
-  float frac = 0.f;
+  float frac = 0.f, wide = 0.f;
   // under capture: no event queries, no buffer growth; every buffer the
   // graph records stays allocated for the context's lifetime
   const bool capturing = stream_capturing((hipStream_t)stream);
@@ -1468,6 +1511,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
     mh = std::max(mh, L.H);
     ms = std::max(ms, L.stride);
     frac = std::max(frac, L.win_frac);
+    wide = std::max(wide, L.wide_frac);
     if (L.H * L.stride > bw) bw = L.H * L.stride;
     if ((int64_t)L.W * L.H > mc) mc = (int64_t)L.W * L.H;
   }
@@ -1483,7 +1527,8 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
   // evaluated per trial (no context tables)
   fire_status ps = plan_run(c, bw, mc, mh, ms, n_params, n_sims,
                             nlive == 1 && (!noalloc || override_T != nullptr), &plan, any_dur,
-                            frac);
+                            frac,
+                            capturing || noalloc ? 1.f : wide);
   if (ps != FIRE_OK) return ps;
   uint32_t *spill = c->d_ovf, *retry = c->d_retry, *work = nullptr;
   if (noalloc && (plan.gb || plan.gb2))
@@ -1685,12 +1730,15 @@ fire_status fire_get_schedule(fire_ctx *c, int64_t max_cells, int32_t n_params,
   const int side = (int)std::ceil(std::sqrt((double)max_cells));
   const int stride = (side + 31) / 32;
   harvest_stats(c);
-  float frac = 0.f;
+  float frac = 0.f, wide = 0.f;
   for (const auto &L : c->ls)
-    if (L.live) frac = std::max(frac, L.win_frac);
+    if (L.live) {
+      frac = std::max(frac, L.win_frac);
+      wide = std::max(wide, L.wide_frac);
+    }
   RunPlan plan;
   fire_status ps = plan_run(c, side * stride, max_cells, side, stride, n_params, n_sims, true,
-                            &plan, false, frac);
+                            &plan, false, frac, wide);
   if (ps != FIRE_OK) return ps;
   *out = plan.s;
   out->window = plan.win;

@@ -21,7 +21,7 @@ import sys
 import numpy as np
 import torch
 
-from . import fire, synth
+from . import fire, ga, synth
 
 CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned_schedules.json")
 
@@ -38,82 +38,126 @@ def cells_bucket(cells: int) -> int:
     return b
 
 
-def candidates(table_ok: bool, side: int = 0):
+BETA_STAR = np.array([[-3.0, -0.5, 6.0, 1.0, 2.0]])
+GA_GENERATIONS = 16
+LDS_BYTES = 160 * 1024  # of a gfx950 compute unit
+LDS_MARGIN = 1024  # per workgroup; with every byte of a share taken one fewer is resident
+
+
+def share_queue(wg: int, W: int, H: int, window: int) -> int:
+    """LDS queue entries that leave `wg` workgroups resident on a compute
+    unit: 1024 entries beside a 512x512 bitset are 4 x 40.1 KiB, 256 B more
+    than the LDS, and three were resident (a Monte Carlo batch 15.5 ms; with
+    this share 14.1 ms)."""
+    rows, words = (min(window, H), min(window // 32, -(-W // 32))) if window else (H, -(-W // 32))
+    return min(4096, (LDS_BYTES // wg - LDS_MARGIN - 4 * (rows * words + 16)) // 8 // 8 * 8)
+
+
+def candidates(table_ok: bool, side: int = 0, dims=None):
     """Schedules to time. One simulation per workgroup: workgroup size x
     workgroups per CU x LDS queue capacity x threshold mode x LDS window
     (none, or a quarter, half and three quarters of the lattice side, when
-    that is at least 64 cells). The wavefront-per-simulation kernel is
+    that is at least 64 cells); with the lattice's `dims` also the queue
+    capacity that keeps all the workgroups resident. The wavefront-per-simulation kernel is
     left out: on the calibration batch it was a third slower than the
     workgroup kernel, and it stays off the built-in paths."""
     windows = [0] + sorted({w for w in (side // 4, side // 2, 3 * side // 4)
                             if w >= 64 and w % 32 == 0 and w < side})
     tables = (0, 1) if table_ok else (0,)
     for threads, wg, qcap, win in itertools.product((128, 256, 512, 1024), (1, 2, 4, 5, 8),
-                                                    (1024, 4096), windows):
+                                                    (0, 1024, 4096), windows):
         if threads > 512 and win > 0:
             continue  # the library runs 1024-thread schedules without a window
+        if qcap == 0:
+            qcap = share_queue(wg, *dims, win) if dims else 0
+            if qcap < 64 or qcap in (1024, 4096):
+                continue
         for table in tables:
             yield {"threads": threads, "queue_cap": qcap, "table_mode": table, "wg_per_cu": wg,
                    "window": win, "wave": 0}
 
 
-def time_schedule(g: fire.FireGPU, sched, d_beta, d_sims, n, seed, out, reps=3):
-    """Median milliseconds of `reps` launches (HIP events on the launch
-    stream) under `sched`, or under the built-in plan when it is None."""
+def time_schedule(g: fire.FireGPU, sched, go, reps=3):
+    """Median milliseconds of `reps` passes of `go(stream)` (HIP events on the
+    launch stream) under `sched`, or under the built-in plan when it is None."""
     if sched is None:
         g.set_schedule(reset=True)
     else:
         g.set_schedule(**sched)
     stream = torch.cuda.current_stream()
-    g.run_dev(d_beta, d_sims, n, seed, out, stream=stream)  # warm-up (allocations)
+    go(stream)  # warm-up (allocations)
     g.sync()
     ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
           for _ in range(reps)]
     for a, b in ev:
         a.record(stream)
-        g.run_dev(d_beta, d_sims, n, seed, out, stream=stream)
+        go(stream)
         b.record(stream)
     g.sync()
     return float(np.median([a.elapsed_time(b) for a, b in ev]))
 
 
 def tune(g: fire.FireGPU, lid: int, sims: np.ndarray, betas: np.ndarray, seed: int,
-         log=None):
-    """Tune one size class (all sims on landscape `lid`). Returns (best, table)."""
+         log=None, kind="replicate"):
+    """Tune one size class (all sims on landscape `lid`). A population is timed
+    as a GA's first generations: the prior's vectors alone have the longest
+    fires, and favour schedules that are slower on the later ones. Replicates
+    are timed as one fire and the batch, which the class serves both (128
+    threads at 512x512: the batch 2% faster, one fire 11% slower than 256).
+    Returns (best, table)."""
     n = len(sims)
     d_sims = torch.from_numpy(np.ascontiguousarray(sims).view(np.uint8).copy()).to(g.device)
     d_beta = torch.from_numpy(np.ascontiguousarray(betas, dtype=np.float64)).to(g.device)
     out = torch.empty((n, 24), dtype=torch.uint8, device=g.device)
-    ref = None
     rows = []
     side = max(g.dims[lid])
     W, H = g.dims[lid]
+
+    def go(st):
+        if kind == "replicate":
+            g.run_dev(d_beta, d_sims, 1, seed, out, stream=st)
+        g.run_dev(d_beta, d_sims, n, seed, out, stream=st)
+
+    tid = None
+    if kind == "population":
+        R = n // len(betas)
+        ign = (int(sims[0]["ign_x"]), int(sims[0]["ign_y"]))
+        _, maps = g.run(BETA_STAR, fire.make_sims(1, lid, -1, ign), seed, want_maps=True)
+        g.sync()
+        words = H * ((W + 31) // 32)
+        tid = g.load_target(lid, maps[0].cpu().numpy().view(np.uint32)[:words].reshape(H, -1))
+        out = torch.empty((GA_GENERATIONS, len(betas), R), dtype=torch.float64, device=g.device)
+
+        def go(st):
+            out.copy_(ga.run_batched(g, lid, tid, ign, betas, R=R, generations=GA_GENERATIONS,
+                                     sim_seed=seed, ga_seed=seed, stream=st)[1].reshape(out.shape))
+
     # the built-in plan first (its window size is not among the grid's)
     g.set_schedule(reset=True)
     builtin = g.get_schedule(W * H, len(betas), n)
-    ms = time_schedule(g, None, d_beta, d_sims, n, seed, out)
+    ms = time_schedule(g, None, go)
     ref = out.clone()
     rows.append((ms, dict(builtin, builtin=True)))
     if log:
         log(f"{ms:8.3f} ms  built-in {builtin}")
     table_ok = len(betas) <= 8 or n >= 8 * len(betas)
-    for sched in candidates(table_ok=table_ok, side=side):
+    for sched in candidates(table_ok=table_ok, side=side, dims=(W, H)):
         if log:
             log(f"timing {sched}")
         try:
-            ms = time_schedule(g, sched, d_beta, d_sims, n, seed, out)
+            ms = time_schedule(g, sched, go)
         except fire.FireError as e:  # LDS budget exceeded for this shape
             if log:
                 log(f"skip {sched}: {e}")
             continue
-        if ref is None:
-            ref = out.clone()
-        elif not torch.equal(out, ref):
+        if not torch.equal(out, ref):
             raise RuntimeError(f"schedule {sched} changed the results")
         rows.append((ms, sched))
         if log:
             log(f"{ms:8.3f} ms  {sched}")
     g.set_schedule(reset=True)
+    if tid is not None:
+        g.free_target(tid)
     rows.sort(key=lambda r: r[0])
     return rows[0][1], rows
 
@@ -149,11 +193,10 @@ def workloads():
     parameter rows, descriptors-builder)."""
     from . import scan
     rng = np.random.default_rng(7)
-    beta_star = np.array([[-3.0, -0.5, 6.0, 1.0, 2.0]])
     for W, H, seed in ((128, 128, 101), (256, 256, 102), (512, 512, 102)):
         ls = synth.make_landscape(W, H, seed)
         c = synth.ignition_site(ls)
-        yield ("replicate", ls, f"{W}x{H}", beta_star,
+        yield ("replicate", ls, f"{W}x{H}", BETA_STAR,
                lambda lid, c=c: fire.make_sims(1280, lid, -1, c))
         pop = np.clip(rng.normal(0.0, 5.0, size=(64, 5)), -30, 30)
         yield ("population", ls, f"{W}x{H}", pop,
@@ -192,7 +235,7 @@ def main():
         lid = g.load_landscape(ls)
         sims = make(lid)
         log(f"{label}, {kind}: {len(betas)} parameter vector(s), {len(sims)} simulations")
-        best, rows = tune(g, lid, sims, betas, 0x5EED0001, log=log)
+        best, rows = tune(g, lid, sims, betas, 0x5EED0001, log=log, kind=kind)
         b = str(cells_bucket(W * H))
         builtin_ms = next(ms for ms, s in rows if s.get("builtin"))
         if best.get("builtin"):

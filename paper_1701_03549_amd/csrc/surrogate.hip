@@ -736,12 +736,32 @@ __global__ __launch_bounds__(256) void upconv_kernel(const uint16_t *src, const 
     }
 }
 
+// 1 / x for x in [1, 3], one Newton step on the hardware's reciprocal
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+
+// log(1 + e) for e in [0, 1] (NaN to NaN): 2 atanh(s), s = e / (2 + e) <= 1/3,
+// by its series in s^2 up to s^17 (the next term is below 2^-33 of the sum).
+__device__ __forceinline__ float log1p_unit(float e) {
+  const float s = e * recip(2.0f + e), q = s * s;
+  float p = 1.0f / 17.0f;
+#pragma unroll
+  for (int k = 15; k >= 3; k -= 2) p = fmaf(p, q, 1.0f / (float)k);
+  return 2.0f * fmaf(p * q, s, s);
+}
+
 // Last layer, one output channel, S = 64: an MFMA would fill one row of 16, so
-// a thread takes an input cell and computes its four output pixels on VALU.
-// With nearest upsampling the nine taps of a pixel read four cells, and the
-// taps on one cell are added first (fp32): 32 products a pixel. The epilogue
-// is fused: TRAIN the map loss and its gradient, dz = w (sigmoid(z) - y) / n in
-// bf16, the workgroup's partial loss to partial[block]; else sigmoid(z).
+// a thread takes two adjacent input cells and computes their eight output
+// pixels on VALU. With nearest upsampling the nine taps of a pixel read four
+// cells, and the taps on one cell are added first (fp32): 32 products a pixel.
+// The epilogue is fused: TRAIN the map loss and its gradient, dz = w (sigmoid(z)
+// - y) / n in bf16, the workgroup's partial loss to partial[block]; else
+// sigmoid(z). What bounds it is the epilogue's VALU work on 8.4 M pixels (512
+// maps): 40 us with one exponential, two Newton reciprocals and a series a
+// pixel, 53 us with two exponentials, a division and the library's log1p. One
+// cell a thread (twice the LDS reads of weights) is 1 us slower.
 constexpr int kLastS = 64, kLastBand = 16, kLastBands = kLastS / kLastBand;  // cell rows a workgroup
 template <bool TRAIN>
 __global__ __launch_bounds__(256) void last_layer_kernel(const uint16_t *src, const uint16_t *Kb,
@@ -767,50 +787,69 @@ __global__ __launch_bounds__(256) void last_layer_kernel(const uint16_t *src, co
   const float bc = bias[0];
   __syncthreads();
   float acc_loss = 0.0f;
-  for (int q = t; q < kLastBand * S; q += 256) {
-    const int r = q / S, X = q % S;
-    float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const bool words = (reinterpret_cast<uintptr_t>(y_map) & 3) == 0;
+  for (int q = t; q < kLastBand * S / 2; q += 256) {
+    const int r = q / (S / 2), X = q % (S / 2) * 2;
+    float z[2][4];  // [cell][parity]
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) z[h][p] = 0.0f;
     const uint32_t *cw = reinterpret_cast<const uint32_t *>(&cells[r * kLd + X]);
     // two channels at a time (all eight unrolled, the compiler keeps the 128
     // weights in registers and two waves a SIMD)
 #pragma unroll 1
     for (int c = 0; c < kConvCi; c += 2) {
-      uint32_t d[9];
+      uint32_t d[12];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) d[k] = cw[((k / 3) * kLd + k % 3) * 4 + c / 2];
+      for (int k = 0; k < 12; ++k) d[k] = cw[((k / 4) * kLd + k % 4) * 4 + c / 2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        float v[9];
+        float v[12];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) v[k] = h ? bf16_hi(d[k]) : bf16_lo(d[k]);
+        for (int k = 0; k < 12; ++k) v[k] = h ? bf16_hi(d[k]) : bf16_lo(d[k]);
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
           const float4 k4 = wk[p][c + h];
-          const int o = 3 * (p >> 1) + (p & 1);
-          z[p] = fmaf(k4.x, v[o], z[p]);
-          z[p] = fmaf(k4.y, v[o + 1], z[p]);
-          z[p] = fmaf(k4.z, v[o + 3], z[p]);
-          z[p] = fmaf(k4.w, v[o + 4], z[p]);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int o = 4 * (p >> 1) + (p & 1) + e;
+            z[e][p] = fmaf(k4.x, v[o], z[e][p]);
+            z[e][p] = fmaf(k4.y, v[o + 1], z[e][p]);
+            z[e][p] = fmaf(k4.z, v[o + 4], z[e][p]);
+            z[e][p] = fmaf(k4.w, v[o + 5], z[e][p]);
+          }
         }
       }
     }
 #pragma unroll
     for (int py = 0; py < 2; ++py) {
-      const int64_t o = ((int64_t)b * O + 2 * (Y0 + r) + py) * O + 2 * X;
+      const int64_t o = ((int64_t)b * O + 2 * (Y0 + r) + py) * O + 2 * X;  // a multiple of 4
+      uint32_t y = 0;
       if constexpr (TRAIN) {
-        float dz[2];
+        if (words) y = *reinterpret_cast<const uint32_t *>(y_map + o);
+        else
 #pragma unroll
-        for (int px = 0; px < 2; ++px) {
-          const float zi = z[2 * py + px] + bc, yi = y_map[o + px] ? 1.0f : 0.0f;
-          acc_loss += fmaxf(zi, 0.0f) - zi * yi + log1pf(expf(-fabsf(zi)));
-          const float sg = 1.0f / (1.0f + expf(-zi));
-          dz[px] = w_map * (sg - yi) * inv_n;
-        }
-        *reinterpret_cast<uint32_t *>(gz + o) = pack_bf16(dz[0], dz[1]);
-      } else {
-        map[o] = 1.0f / (1.0f + expf(-(z[2 * py] + bc)));
-        map[o + 1] = 1.0f / (1.0f + expf(-(z[2 * py + 1] + bc)));
+          for (int i = 0; i < 4; ++i) y |= (uint32_t)y_map[o + i] << (8 * i);
       }
+      float out[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // one exponential for the sigmoid and the loss
+        const float zi = z[i >> 1][2 * py + (i & 1)] + bc, ex = expf(-fabsf(zi));
+        const float rc = recip(1.0f + ex), sg = zi >= 0.0f ? rc : ex * rc;
+        out[i] = sg;
+        if constexpr (TRAIN) {
+          const float yi = (y >> (8 * i)) & 0xFFu ? 1.0f : 0.0f;
+          acc_loss += fmaxf(zi, 0.0f) - zi * yi + log1p_unit(ex);
+          out[i] = w_map * (sg - yi) * inv_n;
+        }
+      }
+      if constexpr (TRAIN)
+        *reinterpret_cast<uint2 *>(gz + o) = make_uint2(pack_bf16(out[0], out[1]), pack_bf16(out[2], out[3]));
+      else
+#pragma unroll
+        for (int i = 0; i < 4; ++i) map[o + i] = out[i];
     }
   }
   if constexpr (TRAIN) {

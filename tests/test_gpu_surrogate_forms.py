@@ -113,3 +113,29 @@ def test_hidden_layers_gradients_at_workgroup_edges(B, use_map):
     if not use_map:
         assert all(not np.any(got[k]) for k in ("Wd", "cd", "K1", "k1", "K2", "k2", "K3", "k3"))
     net.close()
+
+
+@pytest.mark.parametrize("bias", [-150.0, -3.0, 0.0, 3.0, 150.0])
+def test_map_loss_at_large_logits(bias):
+    """The map loss, its bias gradient and the maps where the sigmoid is 0 or 1
+    to fp32: the reference's values, and no NaN or infinity."""
+    import torch
+    from paper_1701_03549_amd import nn
+    B = 2
+    net = nn.Surrogate(max_batch=B, lattice=(256, 256), w_map=0.5, seed=14)
+    p = net.get_params()
+    p[-1] = bias
+    net.set_params(p)
+    x, y = _rows(B, 77)
+    m = (np.random.default_rng(3).random((B, 128, 128)) < 0.4).astype(np.uint8)
+    loss, g = net.gradients(torch.from_numpy(x), torch.from_numpy(y), torch.from_numpy(m).cuda())
+    _, want, ref = S.loss_and_grads(p.cpu().numpy().astype(np.float64), x, y, m, 256, 256, 0.5, bf16=True)
+    # 32768 terms in fp32; dz in bf16, whose rounding errors (2^-9) average out
+    # over as many pixels but are all alike where the sigmoid is 0 or 1
+    assert abs(float(loss[1]) - want) <= 1e-3 * abs(want)
+    assert abs(float(g[-1]) - float(np.asarray(ref)[-1])) <= 2.0 ** -8 * abs(float(np.asarray(ref)[-1]))
+    assert bool(torch.isfinite(g).all())
+    _, maps = net.forward(torch.from_numpy(x), want_map=True)
+    z = S.forward(p.cpu().numpy().astype(np.float64), x, 256, 256, bf16=True)["z"]
+    assert np.allclose(maps.cpu().numpy().reshape(z.shape), 1 / (1 + np.exp(-z)), atol=2e-3)
+    net.close()

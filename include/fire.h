@@ -178,11 +178,11 @@ typedef struct {
  *          map starts at out_maps + i*map_words
  *   map_words  words reserved per map; must be >= H*ceil(W/32) of every
  *          sim's landscape when out_maps != NULL
- * With one parameter vector, simulations are grouped by landscape (by
- * size when more than 8 landscapes are used) and each group runs as its
- * own persistent launch with LDS sized for it, on internal streams forked
- * from and joined back to `stream`. With several parameter vectors the
- * batch runs as one persistent launch whose simulations start in
+ * With one parameter vector, a batch of at most 8 simulations is grouped
+ * by landscape and each group runs as its own persistent launch with LDS
+ * sized for it, on internal streams forked from and joined back to
+ * `stream`; a larger batch is one persistent launch. With several parameter
+ * vectors the batch is one launch, whose simulations start in
  * decreasing order of expected fire size (burnable cells times the Eq. 1
  * probability averaged over the landscape's forest and other burnable
  * cells, each at the landscape's mean aspect and slope terms), so that

@@ -1317,8 +1317,7 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
   // one launch (size classes would run one after another: each persistent
   // launch fills the GPU). Results do not depend on the order.
   const bool lpt = n_params > 1;
-  // Size classes: simulations grouped by landscape (by size when there are
-  // more landscapes than concurrent launches), each class run by its own
+  // Size classes: simulations grouped by landscape, each class run by its own
   // persistent launch with LDS sized for that class.
   std::vector<int> cls_of_ls(c->ls.size(), -1);
   std::vector<int64_t> cls_cells;
@@ -1329,7 +1328,10 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
     const int l = sims[i].landscape_id;
     if (cls_of_ls[l] == -1) { cls_of_ls[l] = -2; ls_ids.push_back(l); }
   }
-  const bool per_ls = (int)ls_ids.size() <= kMaxClasses && !(lpt && ls_ids.size() > 1);
+  // A class per landscape: for one landscape, or a batch of at most kMaxClasses
+  // simulations. Larger batches on several landscapes take one launch: each
+  // class's spill area is sized for a full grid, and eight of them may not fit.
+  const bool per_ls = ls_ids.size() == 1 || (n_sims <= kMaxClasses && !lpt);
   if (per_ls) {
     for (int l : ls_ids) {
       cls_of_ls[l] = (int)cls_cells.size();

@@ -1655,7 +1655,13 @@ fire_status fire_nn_forward(fire_nn *nn, const float *x, int32_t B, float *out_t
     return nn_fail(nn, FIRE_E_INVALID, "bad batch (1..%d) or null pointer", nn->cfg.max_batch);
   NN_HIP(nn, hipSetDevice(nn->device));
   hipStream_t s = (hipStream_t)stream;
-  NN_HIP(nn, forward(nn, x, B, s, out_map != nullptr, false, out_t));
+  // The launch reads some rows of x after it has written other rows' scores:
+  // scores that share memory with x go through the handle's own buffer.
+  const uintptr_t xa = (uintptr_t)x, ta = (uintptr_t)out_t;
+  const bool shared = ta < xa + sizeof(float) * FIRE_NN_IN * (size_t)B && xa < ta + sizeof(float) * (size_t)B;
+  NN_HIP(nn, forward(nn, x, B, s, out_map != nullptr, false, shared ? nn->t : out_t));
+  if (shared)
+    NN_HIP(nn, hipMemcpyAsync(out_t, nn->t, sizeof(float) * (size_t)B, hipMemcpyDeviceToDevice, s));
   if (out_map) {
     hipLaunchKernelGGL((last_layer_kernel<false>), dim3(kLastBands * B), dim3(256), 0, s,
                        nn->d2b, nn->wb + nn->L.K3.off, nn->w + nn->L.k3.off, nullptr, 0.0f, 0.0f,

@@ -726,10 +726,25 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
 #endif
     };
     // the neighbourhood's clear bits (cells that may ignite): 0..2 the row
-    // above (west to east), 3 and 5 the cell's own row, 6..8 the row below
-    auto hood_clear = [&](const Hood &h, int x, int y) -> uint32_t {
+    // above (west to east), 3 and 5 the cell's own row, 6..8 the row below.
+    // Global bitsets: a step of the smallest fronts (`few`, two lanes a cell)
+    // waits for L2, so there all six words are read at once and all six ORs
+    // issued at once, as in LDS; longer fronts leave out the second words
+    // that no bit reaches, which is less traffic but a second wait. One fire
+    // of 92 steps and 38 cells a step on a 1600x1600 lattice, the table's
+    // 103 us included: 379 us with the waits, 304 us without; 32 fires across
+    // it, fronts of 1620 cells: 17.9 ms either way.
+    auto hood_clear = [&](auto few, const Hood &h, int x, int y) -> uint32_t {
       uint32_t lo[3], hi[3];
-      if constexpr (GB) {
+      if constexpr (GB && decltype(few)::value) {
+        // (the words before and after the bitset are not its own: bits that
+        // lie outside the lattice)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+          lo[r] = bload(max(h.w[r], 0));
+          hi[r] = bload(min(h.w[r] + 1, wwords - 1));
+        }
+      } else if constexpr (GB) {
         // the second word only where the three bits reach it (it need not
         // exist otherwise)
 #pragma unroll
@@ -789,7 +804,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
           thr[i] = load_x4(table + (s_lin * 8u + 4u * (kGroups == 1 ? only : (uint32_t)i)));
       }
       h = hood(x, y);
-      uint32_t elig = hood_clear(h, x, y);
+      uint32_t elig = hood_clear(one, h, x, y);
       if (edge) elig = 0u;
       uint32_t hit = 0;
       auto group = [&](uint32_t g, int i) {
@@ -865,7 +880,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
     // all six are issued without a branch (about 60 cycles each to a wave);
     // an OR of nothing goes to an entry of the current queue, another one for
     // each lane (lanes on one word are served in turn).
-    auto cell_ignite = [&](const Hood &h, uint32_t hit) -> uint32_t {
+    auto cell_ignite = [&](auto few, const Hood &h, uint32_t hit) -> uint32_t {
       uint32_t lo[3], hi[3], old_lo[3], old_hi[3];
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -874,7 +889,14 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         hi[r] = (uint32_t)(m >> 32);
         old_lo[r] = old_hi[r] = 0xFFFFFFFFu;
       }
-      if constexpr (GB) {
+      if constexpr (GB && decltype(few)::value) {
+        // (an OR of nothing: another word for each lane)
+        const int idle = min(tid, wwords - 1);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) old_lo[r] = bor(lo[r] ? h.w[r] : idle, lo[r]);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) old_hi[r] = bor(hi[r] ? h.w[r] + 1 : idle, hi[r]);
+      } else if constexpr (GB) {
 #pragma unroll
         for (int r = 0; r < 3; ++r)
           if (lo[r]) old_lo[r] = bor(h.w[r], lo[r]);
@@ -996,7 +1018,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         if ((uint32_t)wave_first < 2 * n_cur) {
           flag_edge(hit);
           hit &= 0x1FFu;
-          const uint32_t fresh = cell_ignite(h, hit);
+          const uint32_t fresh = cell_ignite(std::true_type{}, h, hit);
           append(std::true_type{}, g, e_first, fresh, nslot, 2 * n_cur <= 64u);
         }
       } else if (n_cur <= (uint32_t)(kRegRounds * BLOCK) && n_cur <= cap) {
@@ -1022,7 +1044,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         for (int rr = 0; rr < kRegRounds; ++rr) {
           if (wave_first + rr * BLOCK >= (int)n_cur) break;
           flag_edge(hit[rr]);
-          const uint32_t fresh = cell_ignite(h[rr], hit[rr] & 0x1FFu);
+          const uint32_t fresh = cell_ignite(std::false_type{}, h[rr], hit[rr] & 0x1FFu);
           append(std::false_type{}, 0u, ent[rr], fresh, nslot, n_cur <= 64u);
         }
       } else {
@@ -1047,7 +1069,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
             if (WIN && near_edge(x, y)) ctl[kAbort0 + nslot] = 1u;
             const uint32_t m8 = e >> 24;
             const uint32_t hit = (m8 & 15u) | ((m8 & 0xF0u) << 1);
-            if (hit) fresh = cell_ignite(hood(x, y), hit);
+            if (hit) fresh = cell_ignite(std::false_type{}, hood(x, y), hit);
           }
           append(std::false_type{}, 0u, e, fresh, nslot, false);
         }

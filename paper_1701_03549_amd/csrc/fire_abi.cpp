@@ -453,7 +453,9 @@ int batch_kind(int32_t n_params, int32_t n_sims) {
 // Launch plan for simulations on landscapes of at most max_h rows of
 // max_stride bitset words (bitset_words = the largest H * stride) and
 // max_cells cells. wide_frac: the repeated share of runs in the wide window (1:
-// no such window, for callers whose buffers are sized by an earlier plan).
+// no such window, for callers whose buffers are sized by an earlier plan and for
+// launches that report no repeats, several landscapes in one: fires that leave
+// it would be run twice on every call).
 fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h,
                      int max_stride, int32_t n_params, int32_t n_sims, bool table_allowed,
                      RunPlan *out, bool dur = false, float win_frac = 0.f, float wide_frac = 1.f) {
@@ -1383,7 +1385,7 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
   for (int l : ls_ids) {
     const int k = cls_of_ls[l];
     cls_frac[k] = std::max(cls_frac[k], c->ls[l].win_frac);
-    cls_wide[k] = std::max(cls_wide[k], c->ls[l].wide_frac);
+    cls_wide[k] = per_ls ? c->ls[l].wide_frac : 1.f;
     cls_lid[k] = per_ls ? l : -1;
   }
   for (int k = 0; k < n_cls; ++k) {
@@ -1513,7 +1515,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
     mh = std::max(mh, L.H);
     ms = std::max(ms, L.stride);
     frac = std::max(frac, L.win_frac);
-    wide = std::max(wide, L.wide_frac);
+    wide = L.wide_frac;  // (read when it is the only one)
     if (L.H * L.stride > bw) bw = L.H * L.stride;
     if ((int64_t)L.W * L.H > mc) mc = (int64_t)L.W * L.H;
   }
@@ -1529,8 +1531,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
   // evaluated per trial (no context tables)
   fire_status ps = plan_run(c, bw, mc, mh, ms, n_params, n_sims,
                             nlive == 1 && (!noalloc || override_T != nullptr), &plan, any_dur,
-                            frac,
-                            capturing || noalloc ? 1.f : wide);
+                            frac, capturing || noalloc || nlive != 1 ? 1.f : wide);
   if (ps != FIRE_OK) return ps;
   uint32_t *spill = c->d_ovf, *retry = c->d_retry, *work = nullptr;
   if (noalloc && (plan.gb || plan.gb2))
@@ -1733,10 +1734,11 @@ fire_status fire_get_schedule(fire_ctx *c, int64_t max_cells, int32_t n_params,
   const int stride = (side + 31) / 32;
   harvest_stats(c);
   float frac = 0.f, wide = 0.f;
+  int nlive = 0;
   for (const auto &L : c->ls)
     if (L.live) {
       frac = std::max(frac, L.win_frac);
-      wide = std::max(wide, L.wide_frac);
+      wide = nlive++ ? 1.f : L.wide_frac;  // (as in fire_run_dev)
     }
   RunPlan plan;
   fire_status ps = plan_run(c, side * stride, max_cells, side, stride, n_params, n_sims, true,

@@ -44,7 +44,7 @@ int blocks_for(int64_t n, int t = 256) {
 
 // ---------------------------------------------------------------------------
 // GEMM: 64x64 output tile per workgroup of 4 waves, each wave one 32x32 MFMA
-// tile; K staged through two LDS buffers 32 at a time (the next tile's
+// tile; K staged through two LDS buffers 32 or 64 at a time (the next tile's
 // global loads are in flight while the current one is multiplied). Both
 // operands are stored in LDS as [row][k] (A rows are m, B rows are n), so
 // that each lane's 8 consecutive k of a fragment are contiguous. A thread
@@ -146,33 +146,30 @@ struct GemmBatch {
   int first[kMaxGemms + 1];
 };
 
-// kStages tiles of kTK per LDS buffer: their loads are in flight together, so
-// a workgroup waits for memory once in 64 k (a weight gradient over 512 rows
-// took 16 waits of about 1.1 us with one tile a buffer).
-constexpr int kStages = 2;
-
-template <int AM, int BM>
-__device__ __forceinline__ void gemm_tile(const GemmArgs &q, int tile) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][kStages][kTM * kLdt];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][kStages][kTN * kLdt];
+// STAGES tiles of kTK per LDS buffer. With two, their loads are in flight
+// together, so a workgroup waits for memory once in 64 k (a weight gradient over
+// 512 rows took 16 waits of about 1.1 us with one tile a buffer); but twice the
+// LDS leaves 4 workgroups a compute unit in place of 8 (two_stages).
+template <int AM, int BM, int STAGES>
+__device__ __forceinline__ void gemm_tile(const GemmArgs &q, int m0, int n0) {
+  __shared__ __attribute__((aligned(16))) uint16_t As[2][STAGES][kTM * kLdt];
+  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][STAGES][kTN * kLdt];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nt = (q.N + kTN - 1) / kTN;
-  const int m0 = tile / nt * kTM, n0 = tile % nt * kTN;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
   f32x16_t acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  uint16_t va[kStages][8], vb[kStages][8];
+  uint16_t va[STAGES][8], vb[STAGES][8];
   auto load = [&](int k0) {
 #pragma unroll
-    for (int j = 0; j < kStages; ++j) {
+    for (int j = 0; j < STAGES; ++j) {
       tile_load<AM>(q.A, q.sam, q.sak, m0, q.M, k0 + j * kTK, q.K, tid, va[j]);
       tile_load<BM>(q.B, q.sbn, q.sbk, n0, q.N, k0 + j * kTK, q.K, tid, vb[j]);
     }
   };
   auto store = [&](int buf) {
 #pragma unroll
-    for (int j = 0; j < kStages; ++j) {
+    for (int j = 0; j < STAGES; ++j) {
       tile_store<AM>(As[buf][j], tid, va[j]);
       tile_store<BM>(Bs[buf][j], tid, vb[j]);
     }
@@ -182,11 +179,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &q, int tile) {
   __syncthreads();
   const int half = lane >> 5, r = lane & 31;
   int buf = 0;
-  for (int k0 = 0; k0 < q.K; k0 += kStages * kTK) {
-    const bool more = k0 + kStages * kTK < q.K;
-    if (more) load(k0 + kStages * kTK);
+  for (int k0 = 0; k0 < q.K; k0 += STAGES * kTK) {
+    const bool more = k0 + STAGES * kTK < q.K;
+    if (more) load(k0 + STAGES * kTK);
 #pragma unroll
-    for (int j = 0; j < kStages; ++j) {
+    for (int j = 0; j < STAGES; ++j) {
       if (k0 + j * kTK >= q.K) break;
 #pragma unroll
       for (int kk = 0; kk < kTK; kk += 16) {
@@ -217,9 +214,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs &q, int tile) {
   }
 }
 
-template <int AM, int BM>
+template <int AM, int BM, int STAGES>
 __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs q) {
-  gemm_tile<AM, BM>(q, blockIdx.x);
+  gemm_tile<AM, BM, STAGES>(q, (int)blockIdx.y * kTM, (int)blockIdx.x * kTN);
 }
 
 template <int AM, int BM>
@@ -227,7 +224,8 @@ __global__ __launch_bounds__(256) void gemm_batch_kernel(GemmBatch batch) {
   int i = 0;
 #pragma unroll
   for (int k = 1; k < kMaxGemms; ++k) i += (int)blockIdx.x >= batch.first[k] ? 1 : 0;
-  gemm_tile<AM, BM>(batch.p[i], (int)blockIdx.x - batch.first[i]);
+  const int tile = (int)blockIdx.x - batch.first[i], nt = (batch.p[i].N + kTN - 1) / kTN;
+  gemm_tile<AM, BM, 2>(batch.p[i], tile / nt * kTM, tile % nt * kTN);
 }
 
 int64_t gemm_tiles(const GemmArgs &q) {
@@ -250,6 +248,15 @@ hipError_t gemm_batch(const GemmArgs *q, int n, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether a product takes two tiles a buffer: where a compute unit has one
+// workgroup at most, nothing else hides its waits (512x2048x256, B transposed:
+// 6.4 us with two, 6.7 with one), and a long contraction repays the workgroups
+// that the LDS takes (2048x2048x2048: 39.8 and 45.1 us). Short contractions
+// only pay for the second tile (300x4000x32: 6.0 and 4.9 us), and many tiles hide
+// the waits themselves (65536x256x256: 37.1 and 34.2 us, 65536x2048x64: 175 and
+// 139 us; at 512 tiles and K = 256 the two are within 3%).
+bool two_stages(const GemmArgs &q) { return q.K >= 1024 || (q.K >= 256 && gemm_tiles(q) <= 256); }
+
 // how an operand of `rows` x `kdim` with strides (sr, sk) is loaded
 int load_mode(const uint16_t *p, int64_t sr, int64_t sk) {
   if ((reinterpret_cast<uintptr_t>(p) & 15u) != 0) return kElementwise;
@@ -258,13 +265,20 @@ int load_mode(const uint16_t *p, int64_t sr, int64_t sk) {
   return kElementwise;
 }
 
-template <int AM>
+template <int AM, int STAGES>
 hipError_t gemm_b(int bm, const GemmArgs &q, hipStream_t s) {
-  const dim3 grid((unsigned)gemm_tiles(q));
-  if (bm == kAlongK) hipLaunchKernelGGL((gemm_kernel<AM, kAlongK>), grid, dim3(256), 0, s, q);
-  else if (bm == kAlongRows) hipLaunchKernelGGL((gemm_kernel<AM, kAlongRows>), grid, dim3(256), 0, s, q);
-  else hipLaunchKernelGGL((gemm_kernel<AM, kElementwise>), grid, dim3(256), 0, s, q);
+  const dim3 grid((unsigned)((q.N + kTN - 1) / kTN), (unsigned)((q.M + kTM - 1) / kTM));
+  if (bm == kAlongK) hipLaunchKernelGGL((gemm_kernel<AM, kAlongK, STAGES>), grid, dim3(256), 0, s, q);
+  else if (bm == kAlongRows) hipLaunchKernelGGL((gemm_kernel<AM, kAlongRows, STAGES>), grid, dim3(256), 0, s, q);
+  else hipLaunchKernelGGL((gemm_kernel<AM, kElementwise, STAGES>), grid, dim3(256), 0, s, q);
   return hipGetLastError();
+}
+
+template <int STAGES>
+hipError_t gemm_a(int am, int bm, const GemmArgs &q, hipStream_t s) {
+  if (am == kAlongK) return gemm_b<kAlongK, STAGES>(bm, q, s);
+  if (am == kAlongRows) return gemm_b<kAlongRows, STAGES>(bm, q, s);
+  return gemm_b<kElementwise, STAGES>(bm, q, s);
 }
 
 hipError_t gemm(int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak,
@@ -272,9 +286,7 @@ hipError_t gemm(int M, int N, int K, const uint16_t *A, int64_t sam, int64_t sak
                 const float *bias, int relu, int accumulate, uint16_t *Cb, hipStream_t s) {
   const GemmArgs q{M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, relu, accumulate, Cb};
   const int am = load_mode(A, sam, sak), bm = load_mode(B, sbn, sbk);
-  if (am == kAlongK) return gemm_b<kAlongK>(bm, q, s);
-  if (am == kAlongRows) return gemm_b<kAlongRows>(bm, q, s);
-  return gemm_b<kElementwise>(bm, q, s);
+  return two_stages(q) ? gemm_a<2>(am, bm, q, s) : gemm_a<1>(am, bm, q, s);
 }
 
 // ---------------------------------------------------------------------------

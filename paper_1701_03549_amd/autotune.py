@@ -77,7 +77,7 @@ def candidates(table_ok: bool, side: int = 0, dims=None):
                    "window": win, "wave": 0}
 
 
-def time_schedule(g: fire.FireGPU, sched, go, reps=3):
+def time_passes(g: fire.FireGPU, sched, go, reps=3):
     """Median milliseconds of `reps` passes of `go(stream)` (HIP events on the
     launch stream) under `sched`, or under the built-in plan when it is None."""
     if sched is None:
@@ -97,12 +97,18 @@ def time_schedule(g: fire.FireGPU, sched, go, reps=3):
     return float(np.median([a.elapsed_time(b) for a, b in ev]))
 
 
+def time_schedule(g: fire.FireGPU, sched, d_beta, d_sims, n, seed, out, reps=3):
+    """time_passes of one launch of n device descriptors."""
+    return time_passes(g, sched, lambda st: g.run_dev(d_beta, d_sims, n, seed, out, stream=st), reps)
+
+
 def tune(g: fire.FireGPU, lid: int, sims: np.ndarray, betas: np.ndarray, seed: int,
-         log=None, kind="replicate"):
-    """Tune one size class (all sims on landscape `lid`). A population is timed
+         log=None, kind=None):
+    """Tune one size class (all sims on landscape `lid`), timed as the batch
+    itself, or as its `kind` is used. A "population" is timed
     as a GA's first generations: the prior's vectors alone have the longest
-    fires, and favour schedules that are slower on the later ones. Replicates
-    are timed as one fire and the batch, which the class serves both (128
+    fires, and favour schedules that are slower on the later ones. "replicate"
+    is timed as one fire and the batch, which the class serves both (128
     threads at 512x512: the batch 2% faster, one fire 11% slower than 256).
     Returns (best, table)."""
     n = len(sims)
@@ -135,7 +141,7 @@ def tune(g: fire.FireGPU, lid: int, sims: np.ndarray, betas: np.ndarray, seed: i
     # the built-in plan first (its window size is not among the grid's)
     g.set_schedule(reset=True)
     builtin = g.get_schedule(W * H, len(betas), n)
-    ms = time_schedule(g, None, go)
+    ms = time_passes(g, None, go)
     ref = out.clone()
     rows.append((ms, dict(builtin, builtin=True)))
     if log:
@@ -145,7 +151,7 @@ def tune(g: fire.FireGPU, lid: int, sims: np.ndarray, betas: np.ndarray, seed: i
         if log:
             log(f"timing {sched}")
         try:
-            ms = time_schedule(g, sched, go)
+            ms = time_passes(g, sched, go)
         except fire.FireError as e:  # LDS budget exceeded for this shape
             if log:
                 log(f"skip {sched}: {e}")

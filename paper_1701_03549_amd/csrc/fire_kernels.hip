@@ -728,15 +728,19 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
     // the neighbourhood's clear bits (cells that may ignite): 0..2 the row
     // above (west to east), 3 and 5 the cell's own row, 6..8 the row below.
     // Global bitsets: a step of the smallest fronts (`few`, two lanes a cell)
-    // waits for L2, so there all six words are read at once and all six ORs
-    // issued at once, as in LDS; longer fronts leave out the second words
-    // that no bit reaches, which is less traffic but a second wait. One fire
-    // of 92 steps and 38 cells a step on a 1600x1600 lattice, the table's
-    // 103 us included: 379 us with the waits, 304 us without; 32 fires across
-    // it, fronts of 1620 cells: 17.9 ms either way.
+    // waits for L2, so there workgroups of 512 threads and more read all six
+    // words at once and issue all six ORs at once, as in LDS; longer fronts,
+    // and the smaller workgroups of which a compute unit holds several, leave
+    // out the second words that no bit reaches, which is less traffic but a
+    // second wait. One fire of 92 steps and 38 cells a step on a 1600x1600
+    // lattice, the table's 103 us included: 388 us with the waits, 306 us
+    // without; 400 fires of 228 steps at 1300x1000 (512 threads) 2.43 and
+    // 1.77 ms; 8192 of them (128 threads, 10 a compute unit) 5.5 and 8.6 ms;
+    // 32 fires across 1600x1600, fronts of 1620 cells, 17.9 ms either way.
+    constexpr bool kFewGlobal = GB && BLOCK >= 512;
     auto hood_clear = [&](auto few, const Hood &h, int x, int y) -> uint32_t {
       uint32_t lo[3], hi[3];
-      if constexpr (GB && decltype(few)::value) {
+      if constexpr (kFewGlobal && decltype(few)::value) {
         // (the words before and after the bitset are not its own: bits that
         // lie outside the lattice)
 #pragma unroll
@@ -889,7 +893,7 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
         hi[r] = (uint32_t)(m >> 32);
         old_lo[r] = old_hi[r] = 0xFFFFFFFFu;
       }
-      if constexpr (GB && decltype(few)::value) {
+      if constexpr (kFewGlobal && decltype(few)::value) {
         // (an OR of nothing: another word for each lane)
         const int idle = min(tid, wwords - 1);
 #pragma unroll

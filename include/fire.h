@@ -345,7 +345,9 @@ fire_status fire_set_class_schedule(fire_ctx *ctx, int64_t max_cells, int32_t ki
                                     const fire_schedule *s);
 /* The schedule a batch of `n_sims` simulations with `n_params` parameter
  * vectors on a square lattice of `max_cells` cells would use (window: the
- * LDS window side of its first launch, 0 for none). */
+ * LDS window side of its first launch, 0 for none). fire_run, which knows
+ * the parameters, takes no table for at most 8 simulations of one vector
+ * on a lattice of 2^22 cells and more whose fires it expects to be small. */
 fire_status fire_get_schedule(fire_ctx *ctx, int64_t max_cells,
                               int32_t n_params, int32_t n_sims,
                               fire_schedule *out);

@@ -1260,6 +1260,22 @@ static double expected_size(const LandscapeHost &L, const double *b) {
   return (double)L.burnable * p;
 }
 
+// A few small fires on a large lattice read next to nothing of an Eq. 1 table,
+// which is 32 B of every cell: at most kMaxClasses simulations of one vector
+// evaluate their thresholds per trial from kFewTableCells cells on, unless their
+// mean probability (expected_size a burnable cell) comes near the 1/4 above
+// which fires spread across a lattice of eight neighbours. Two fires of tens of
+// steps at 2048x2048: 96 us without a table, 255 us with one; at 4096x4096 225
+// and 930 us; 30 times as long a fire (forest alone burning) 1.27 and 1.87 ms. A
+// fire across 1600x1600 takes 24 ms without and 18 ms with its table, and smaller
+// lattices' tables cost less than the difference between two such fires.
+constexpr int64_t kFewTableCells = (int64_t)1 << 22;
+constexpr double kSmallFireMean = 0.2;
+static bool table_unread(const LandscapeHost &L, const double *b, int32_t n_params, int32_t n_sims) {
+  return n_params == 1 && n_sims <= kMaxClasses && (int64_t)L.W * L.H >= kFewTableCells &&
+         expected_size(L, b) < kSmallFireMean * (double)L.burnable;
+}
+
 fire_status fire_order_sims(fire_ctx *c, const double *betas, int32_t n_params,
                             const fire_sim *sims, int32_t n_sims, int32_t *out_order) {
   if (!c) return FIRE_E_INVALID;
@@ -1388,9 +1404,15 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
     cls_wide[k] = per_ls ? c->ls[l].wide_frac : 1.f;
     cls_lid[k] = per_ls ? l : -1;
   }
+  // (a schedule that the caller set says itself whether it takes tables)
+  bool own_schedule = c->sched_fixed;
+  for (const auto &e : c->class_sched)
+    own_schedule = own_schedule || (e.bucket == cells_bucket(mc) && e.kind == 0);
+  const bool table_ok = one_ls >= 0 && (override_T || own_schedule ||
+                                        !table_unread(c->ls[one_ls], betas, n_params, n_sims));
   for (int k = 0; k < n_cls; ++k) {
     fire_status ps = plan_run(c, cls_words[k], cls_cells[k], cls_h[k], cls_stride[k], n_params,
-                              (int32_t)members[k].size(), one_ls >= 0, &plans[k],
+                              (int32_t)members[k].size(), table_ok, &plans[k],
                               cls_dur[k] != 0, cls_frac[k], cls_wide[k]);
     if (ps != FIRE_OK) return ps;
     spill_total += spill_words(plans[k]);

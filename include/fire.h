@@ -323,9 +323,7 @@ typedef struct {
                             queue_cap (or a window) is run again by the
                             workgroup kernel over the whole lattice, with
                             the same coins and so the same result. The
-                            built-in choice uses it for batches of at most
-                            8 parameter vectors without turn-off times
-                            while such re-runs stay absent.               */
+                            built-in choice does not use it.              */
 } fire_schedule;
 
 /* Fix the schedule used by later fire_run/fire_run_dev calls; NULL

@@ -455,11 +455,6 @@ __device__ __forceinline__ u32x4 load_x4_at(gmem_cu32 *base, uint32_t bytes) {
   return *(gmem_cu32x4 *)((const __attribute__((address_space(1))) char *)base + bytes);
 }
 
-__device__ __forceinline__ uint4 load_rec(const uint4 *base, int64_t t) {
-  gmem_cu32 *q = (gmem_cu32 *)(base + t);
-  return make_uint4(q[0], q[1], q[2], q[3]);
-}
-
 // The vegetation | up-mask word of record t.
 __device__ __forceinline__ uint32_t rec_word(const uint4 *base, int64_t t) {
   return ((gmem_cu32 *)(base + t))[3];
@@ -482,7 +477,7 @@ enum CtlSlot { kSim = 0, kLen0 = 1, kTrials = 4, kNew = 5, kInter = 6, kAbort0 =
                kCtlWords = 16 };
 
 // register-resident rounds of the small-front step (fronts of up to
-// kRegRounds * BLOCK / 2 cells held in the LDS queue)
+// kRegRounds * BLOCK cells, a lane a cell, held in the LDS queue)
 constexpr int kRegRounds = 2;
 
 // GB (global bitset, never with WIN): the burn bitset of the workgroup's
@@ -689,10 +684,9 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
     // frontier length of step k lives in ctl[kLen0 + k % 3]
     int slot = 0;
     bool aborted = false;
-    // a new cell enters the queue with life 0 (not yet known); the first
-    // unit of its entry looks it up in phase 1 of the next step, where the
-    // read overlaps the unit's other reads, and it is needed only after
-    // that phase
+    // a new cell enters the queue with life 0 (not yet known); its (first)
+    // lane looks it up in phase 1 of the next step, where the read overlaps
+    // the lane's other reads, and it is needed only after that phase
     auto resolve_life = [&](uint32_t e, uint32_t i) {
       if (DUR && l_load(cq, i) == 0u)
         l_store(cq, i, life_of((int)(e & 0xFFFu), (int)((e >> 12) & 0xFFFu)));
@@ -851,13 +845,11 @@ __global__ __launch_bounds__(BLOCK) void sim_kernel(SimArgs a) {
           hg &= el;
           unsure &= el;
           while (unsure) {
-            // within the margin: the binary64 threshold (and the coin drawn
-            // again, so that no word is held for this rare case)
+            // within the margin: the binary64 threshold
             const uint32_t bit = unsure & (0u - unsure);
             unsure ^= bit;
             const int k = bit == 2u ? 0 : bit == 4u ? 1 : bit == 32u ? 2 : 3;
-            const Words4 q = philox10(sim_index, step, s_lin, g, a.key0, a.key1);
-            const uint32_t coin = k & 2 ? (k & 1 ? q.v[3] : q.v[2]) : (k & 1 ? q.v[1] : q.v[0]);
+            const uint32_t coin = k & 2 ? (k & 1 ? r.v[3] : r.v[2]) : (k & 1 ? r.v[1] : r.v[0]);
             gmem_cf64 *const b = (gmem_cf64 *)bp;
             const double beta[5] = {b[0], b[1], b[2], b[3], b[4]};
             const int64_t tl = (int64_t)s_lin + s * (k == 0 ? -W : k == 1 ? 1 - W : k == 2 ? 1 : 1 + W);

@@ -645,19 +645,19 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const float *p, int n
 // a training batch of 512 spent 740 of its 890 us in these layers and the map
 // loss: last forward layer 146, its loss and bf16 copy 57, its gradients 94,
 // the other gradients 226, the other forward layers 78 us (rocprofv3). Now the
-// last layer takes 53 with the loss (its exponentials and 32 products a pixel on
-// VALU), its gradients 42 (73 sums a thread on VALU; 84 MB of traffic would
+// last layer takes 40 with the loss (its 32 products and one exponential a pixel
+// on VALU), its gradients 41 (73 sums a thread on VALU; 84 MB of traffic would
 // take 18 at the 4.8 TB/s of a copy), the others 20 + 20 + 10 + 7 and 18 + 8 us,
-// and the batch 442 us.
+// and the whole batch 260 us.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 constexpr int kConvCi = 8, kConvTaps = 9, kConvK = kConvCi * kConvTaps;  // 72
 constexpr int kWgradCols = 80;  // 72 kernel taps, the bias column, padding
 constexpr int kWgradRows = 16;  // output channels, padded
-constexpr int kWgradParts = 2048;
 // workgroups of the gradient kernels that keep sums across samples: each adds
 // its sums once, so a few samples a workgroup pay for it
 constexpr int kConvGrid = 512, kCo1Grid = 1024;
+constexpr int kWgradParts = kConvGrid > kCo1Grid ? kConvGrid : kCo1Grid;
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
 
@@ -755,7 +755,7 @@ __device__ __forceinline__ float recip(float x) {
 }
 
 // log(1 + e) for e in [0, 1] (NaN to NaN): 2 atanh(s), s = e / (2 + e) <= 1/3,
-// by its series in s^2 up to s^17 (the next term is below 2^-33 of the sum).
+// by its series in s^2 up to s^17 (the next term is below 2^-32 of the sum).
 __device__ __forceinline__ float log1p_unit(float e) {
   const float s = e * recip(2.0f + e), q = s * s;
   float p = 1.0f / 17.0f;
@@ -1392,7 +1392,7 @@ struct fire_nn {
   std::string err;
   Layout L;
   float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;  // [total]
-  uint16_t *wb = nullptr;                                        // bf16 copy [total]
+  uint16_t *wb = nullptr;  // bf16 copy [total], of which W2, W3 and the kernels are read
   uint16_t *wt = nullptr;  // bf16 W1, W2, W3 transposed ([out][in]), Wf, Wd
   // activations (max_batch rows)
   uint16_t *xb = nullptr, *h1b = nullptr, *h2b = nullptr, *h3b = nullptr, *d0b = nullptr, *dtb = nullptr;

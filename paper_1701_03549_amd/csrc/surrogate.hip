@@ -224,8 +224,9 @@ __global__ __launch_bounds__(256) void gemm_batch_kernel(GemmBatch batch) {
   int i = 0;
 #pragma unroll
   for (int k = 1; k < kMaxGemms; ++k) i += (int)blockIdx.x >= batch.first[k] ? 1 : 0;
-  const int tile = (int)blockIdx.x - batch.first[i], nt = (batch.p[i].N + kTN - 1) / kTN;
-  gemm_tile<AM, BM, 2>(batch.p[i], tile / nt * kTM, tile % nt * kTN);
+  const GemmArgs &q = batch.p[i];
+  const int tile = (int)blockIdx.x - batch.first[i], nt = (q.N + kTN - 1) / kTN;
+  gemm_tile<AM, BM, 2>(q, tile / nt * kTM, tile % nt * kTN);
 }
 
 int64_t gemm_tiles(const GemmArgs &q) {

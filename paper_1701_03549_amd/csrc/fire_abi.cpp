@@ -70,13 +70,17 @@ struct fire_ctx {
   size_t retry_words = 0;
   // retry counts of window runs, written into host-mapped memory by the
   // re-run launch (read once stat_ev[i] has passed): slot i holds the count
-  // of a launch on landscape stat_ls[i] of stat_n[i] simulations
+  // of a launch on landscape stat_ls[i] (or kMixedStat) of stat_n[i] simulations
   static constexpr int kStatSlots = 16;
   uint32_t *h_stat = nullptr;
   hipEvent_t stat_ev[kStatSlots] = {};
   int stat_ls[kStatSlots] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
   int stat_n[kStatSlots] = {};
   bool stat_wide[kStatSlots] = {};
+  // the repeated share of wide-window runs over several landscapes, whose
+  // counts belong to none of them
+  float mixed_frac = 0.f;
+  int mixed_obs = 0;
   // workgroups of each simulation-kernel variant resident per CU as far as
   // registers allow ([threads 64..1024][table][turn-off times][window];
   // 0 = unknown)
@@ -131,6 +135,9 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kMaxClasses = 8;   // concurrent persistent launches per fire_run
+// whose repeats a launch's count belongs to, besides a landscape's id: none, or
+// a launch over several landscapes
+constexpr int kNoStat = -1, kMixedStat = -2;
 constexpr int kErrWord = 16;     // error flag word in d_work
 constexpr int kWorkWords = 32;
 
@@ -403,6 +410,9 @@ constexpr float kWindowRetryMax = 0.0f;
 // batch has more simulations than these (so that the first window, which kept
 // more resident, was smaller) and unless more than kWideRetryMax of such a run had to
 // be repeated: a repeat costs what its simulation would have cost at first.
+// Launches over several landscapes keep a share of their own (mixed_frac):
+// without one, fires that leave the window were run twice on every call (800
+// fires on two 1000x930 lattices 20.5 ms, whole-lattice 14.4).
 // 8192 simulations of the 1024x1024 ignition scan: 4.8 ms whole-lattice, 3.1 ms
 // in the wide window (128 threads 3.8, 512 threads 3.6 ms; 704 cells a side,
 // two workgroups, 3.8 ms).
@@ -453,9 +463,7 @@ int batch_kind(int32_t n_params, int32_t n_sims) {
 // Launch plan for simulations on landscapes of at most max_h rows of
 // max_stride bitset words (bitset_words = the largest H * stride) and
 // max_cells cells. wide_frac: the repeated share of runs in the wide window (1:
-// no such window, for callers whose buffers are sized by an earlier plan and for
-// launches that report no repeats, several landscapes in one: fires that leave
-// it would be run twice on every call).
+// no such window, for callers whose buffers are sized by an earlier plan).
 fire_status plan_run(fire_ctx *c, int bitset_words, int64_t max_cells, int max_h,
                      int max_stride, int32_t n_params, int32_t n_sims, bool table_allowed,
                      RunPlan *out, bool dur = false, float win_frac = 0.f, float wide_frac = 1.f) {
@@ -714,9 +722,13 @@ fire_status ensure_spill(fire_ctx *c, int64_t words, hipStream_t st) {
 void harvest_stats(fire_ctx *c) {
   for (int i = 0; i < fire_ctx::kStatSlots; ++i) {
     const int l = c->stat_ls[i];
-    if (l < 0 || hipEventQuery(c->stat_ev[i]) != hipSuccess) continue;
+    if (l == kNoStat || hipEventQuery(c->stat_ev[i]) != hipSuccess) continue;
     (void)hipGetLastError();
-    if (l < (int)c->ls.size() && c->ls[l].live && c->stat_n[i] > 0) {
+    if (l == kMixedStat) {
+      const float f = (float)c->h_stat[i] / (float)c->stat_n[i];
+      c->mixed_frac = c->mixed_obs ? 0.5f * c->mixed_frac + 0.5f * f : f;
+      ++c->mixed_obs;
+    } else if (l < (int)c->ls.size() && c->ls[l].live && c->stat_n[i] > 0) {
       LandscapeHost &L = c->ls[l];
       const float f = (float)c->h_stat[i] / (float)c->stat_n[i];
       if (c->stat_wide[i]) {
@@ -727,7 +739,7 @@ void harvest_stats(fire_ctx *c) {
         ++L.win_obs;
       }
     }
-    c->stat_ls[i] = -1;
+    c->stat_ls[i] = kNoStat;
   }
 }
 
@@ -743,7 +755,7 @@ int stat_slot(fire_ctx *c, hipStream_t st) {
   }
   harvest_stats(c);
   for (int i = 0; i < fire_ctx::kStatSlots; ++i)
-    if (c->stat_ls[i] < 0) return i;
+    if (c->stat_ls[i] == kNoStat) return i;
   return -1;
 }
 
@@ -782,7 +794,7 @@ fire_status launch_run(fire_ctx *c, const RunPlan &p, const double *betas_dev,
                        const uint32_t *tables, int64_t table_stride,
                        int32_t table_ls, fire_result *out, uint32_t *out_maps,
                        int64_t map_words, int counter, uint32_t *spill, uint32_t *retry,
-                       hipStream_t st, int stat_lid = -1, uint32_t *work_base = nullptr) {
+                       hipStream_t st, int stat_lid = kNoStat, uint32_t *work_base = nullptr) {
   // work counters: the context's (or, for the no-allocation entry point,
   // words of its scratch)
   uint32_t *const wb = work_base ? work_base : c->d_work;
@@ -810,7 +822,8 @@ fire_status launch_run(fire_ctx *c, const RunPlan &p, const double *betas_dev,
                          p.s2.queue_cap, p.grid2, p.dur, p.bitset_words2, work2, spill);
     b.n_dev = retry;
     b.gbits = p.gb2 ? gbits : nullptr;
-    const int slot = stat_lid >= 0 ? stat_slot(c, st) : -1;
+    const bool counted = stat_lid == kMixedStat ? p.wide : stat_lid != kNoStat;
+    const int slot = counted ? stat_slot(c, st) : -1;
     if (slot >= 0) b.stat_out = c->h_stat + slot;
     HIP_OR_FAIL(c, launch_sim(b, p.s2.threads, tables != nullptr, p.dur, p.grid2, p.lds2, st));
     if (slot >= 0) {
@@ -1068,8 +1081,8 @@ fire_status fire_landscape_set_burn_steps(fire_ctx *c, int32_t id, const uint8_t
   HIP_OR_FAIL(c, hipSetDevice(c->device));
   HIP_OR_FAIL(c, hipDeviceSynchronize());
   LandscapeHost &L = c->ls[id];
-  L.win_frac = L.wide_frac = 0.f;  // fire sizes change with the turn-off times
-  L.win_obs = L.wide_obs = 0;
+  L.win_frac = L.wide_frac = c->mixed_frac = 0.f;  // fire sizes change with the turn-off times
+  L.win_obs = L.wide_obs = c->mixed_obs = 0;
   const int64_t n = (int64_t)L.W * L.H;
   if (!steps || all_one) {
     if (L.burn_steps) HIP_OR_FAIL(c, hipFree(L.burn_steps));
@@ -1397,12 +1410,12 @@ fire_status fire_run(fire_ctx *c, const double *betas, int32_t n_params,
   int64_t spill_total = 0;
   harvest_stats(c);
   std::vector<float> cls_frac(n_cls, 0.f), cls_wide(n_cls, 0.f);
-  std::vector<int> cls_lid(n_cls, -1);
+  std::vector<int> cls_lid(n_cls, kNoStat);
   for (int l : ls_ids) {
     const int k = cls_of_ls[l];
     cls_frac[k] = std::max(cls_frac[k], c->ls[l].win_frac);
-    cls_wide[k] = per_ls ? c->ls[l].wide_frac : 1.f;
-    cls_lid[k] = per_ls ? l : -1;
+    cls_wide[k] = std::max({cls_wide[k], c->ls[l].wide_frac, per_ls ? 0.f : c->mixed_frac});
+    cls_lid[k] = per_ls ? l : kMixedStat;
   }
   // (a schedule that the caller set says itself whether it takes tables)
   bool own_schedule = c->sched_fixed;
@@ -1537,10 +1550,11 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
     mh = std::max(mh, L.H);
     ms = std::max(ms, L.stride);
     frac = std::max(frac, L.win_frac);
-    wide = L.wide_frac;  // (read when it is the only one)
+    wide = std::max(wide, L.wide_frac);
     if (L.H * L.stride > bw) bw = L.H * L.stride;
     if ((int64_t)L.W * L.H > mc) mc = (int64_t)L.W * L.H;
   }
+  if (nlive > 1) wide = std::max(wide, c->mixed_frac);
   if (nlive == 0) return fail(c, FIRE_E_INVALID, "no landscape loaded");
   if (override_T && nlive != 1)
     return fail(c, FIRE_E_INVALID, "thresholds_override needs exactly one loaded landscape");
@@ -1553,7 +1567,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
   // evaluated per trial (no context tables)
   fire_status ps = plan_run(c, bw, mc, mh, ms, n_params, n_sims,
                             nlive == 1 && (!noalloc || override_T != nullptr), &plan, any_dur,
-                            frac, capturing || noalloc || nlive != 1 ? 1.f : wide);
+                            frac, capturing || noalloc ? 1.f : wide);
   if (ps != FIRE_OK) return ps;
   uint32_t *spill = c->d_ovf, *retry = c->d_retry, *work = nullptr;
   if (noalloc && (plan.gb || plan.gb2))
@@ -1602,7 +1616,7 @@ static fire_status run_dev_impl(fire_ctx *c, const double *betas_dev, int32_t n_
   }
   return launch_run(c, plan, betas_dev, n_params, sims_dev, nullptr, n_sims, seed, tables,
                     tstride, tables ? lid : -1, out, out_maps, map_words, 0, spill, retry, st,
-                    nlive == 1 ? lid : -1, work);
+                    nlive == 1 ? lid : kMixedStat, work);
 }
 
 fire_status fire_run_dev(fire_ctx *c, const double *betas_dev, int32_t n_params,
@@ -1760,7 +1774,7 @@ fire_status fire_get_schedule(fire_ctx *c, int64_t max_cells, int32_t n_params,
   for (const auto &L : c->ls)
     if (L.live) {
       frac = std::max(frac, L.win_frac);
-      wide = nlive++ ? 1.f : L.wide_frac;  // (as in fire_run_dev)
+      wide = std::max(wide, nlive++ ? std::max(L.wide_frac, c->mixed_frac) : L.wide_frac);
     }
   RunPlan plan;
   fire_status ps = plan_run(c, side * stride, max_cells, side, stride, n_params, n_sims, true,
